@@ -1,0 +1,547 @@
+// scan_rows.hip -- full selective scan, one wave per sequence (any N; the
+// path of every N but 16, and of the N = 16 forms the other kernels refuse).
+//
+// Same recurrence as scan_full.hip (Appendix A: eq. 3, eq. 4 first line,
+// eq. 6). Lanes own runs of T = 8 (or 4) consecutive positions; a wave walks
+// its sequence in chunks of 64 T positions, sequences of up to 32 T (16 T)
+// positions share a wave, 2 (4) channels of a direction each in a segment of
+// 32 (16) lanes. Per state a lane forms a_i = exp(Delta_i A_n) and
+// b_i = Delta_i B_i u_i for its run and folds them into the run's aggregate,
+// an inclusive DPP scan over the wave (segment) joins the runs, and the lane
+// re-walks its run from the state entering it, accumulating y_i += C_i h_i.
+// The state leaving a chunk is kept per state in lane n of one register.
+//
+// What bounds it: with few states the timescale's softplus (2 of its about 15
+// instructions at quarter rate), the products and the bytes of delta and y,
+// not the recurrence; so delta, B and C are read as whole 16-byte vectors of
+// a run, the next state's B and C (and the next chunk's delta) in flight
+// while the current ones are in use.
+//
+// 2-D layout, planes that fit LDS (kFused): a workgroup owns a channel (2 or
+// 4 short ones) with one wave per direction. The input plane is copied into
+// LDS in both scan orders and each direction leaves its outputs there as a
+// plane of its own; after a barrier the four are summed in the association of
+// the cross-merge, (y0 + y2) + (y1 + y3), and stored. Per-direction outputs
+// never reach memory (the merge pass it replaces moved 32 bytes per pixel and
+// channel). All LDS runs are aligned vectors: the reversed directions start
+// their runs at the padded end of the plane, with identity positions
+// (Delta = 0, B = 0) ahead of the first pixel.
+#include "vmb_internal.h"
+
+namespace vmb {
+namespace {
+
+constexpr int kWave = 64;
+constexpr int kRowWaves = 4;
+constexpr int kRowThreads = kRowWaves * kWave;
+constexpr int kWaveShr1 = 0x138;  // DPP wave_shr:1 (GFX9 encoding)
+
+enum RowMode { kSeq = 0, kFused = 1, kMapRows = 2 };
+
+__device__ __forceinline__ float shr1(float old, float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old),
+                                                                 __builtin_bit_cast(int, v),
+                                                                 kWaveShr1, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __builtin_bit_cast(float,
+                              __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
+// T elements as they lie in memory.
+template <typename Tin, int T>
+struct Run {
+    static constexpr int kWords = T * static_cast<int>(sizeof(Tin)) / 4;
+    uint32_t w[kWords];
+};
+template <int T>
+__device__ __forceinline__ float run_at(const Run<float, T>& r, int i) {
+    return __uint_as_float(r.w[i]);
+}
+template <int T>
+__device__ __forceinline__ float run_at(const Run<bf16_t, T>& r, int i) {
+    return __uint_as_float((i & 1) ? r.w[i / 2] & 0xffff0000u : r.w[i / 2] << 16);
+}
+
+// The run at element offset off from base: one vector when its T elements lie
+// inside the tensor, that is lo <= off and off + T <= hi (they may belong to
+// the next or previous row: positions outside the sequence are never used).
+// At the ends of the tensor the row's own elements [first, last] are read one
+// by one (a rolled loop that shifts them in from the top, to stay small).
+template <int T>
+__device__ __forceinline__ void shift_in(Run<float, T>& r, float e) {
+#pragma unroll
+    for (int i = T - 1; i > 0; --i) r.w[i] = r.w[i - 1];
+    r.w[0] = __float_as_uint(e);
+}
+template <int T>
+__device__ __forceinline__ void shift_in(Run<bf16_t, T>& r, bf16_t e) {
+#pragma unroll
+    for (int i = Run<bf16_t, T>::kWords - 1; i > 0; --i)
+        r.w[i] = (r.w[i] << 16) | (r.w[i - 1] >> 16);
+    r.w[0] = (r.w[0] << 16) | e.bits;
+}
+template <typename Tin, int T>
+__device__ __forceinline__ void load_run(const Tin* base, int off, int lo, int hi, int first,
+                                         int last, Run<Tin, T>& r) {
+    if (off >= lo && off + T <= hi) {
+        __builtin_memcpy(&r, base + off, sizeof(r));
+    } else {
+#pragma unroll
+        for (int i = 0; i < Run<Tin, T>::kWords; ++i) r.w[i] = 0;
+        if (off <= last) {
+#pragma unroll 1
+            for (int i = T - 1; i >= 0; --i) {
+                const int o = off + i < first ? first : (off + i > last ? last : off + i);
+                shift_in<T>(r, base[o]);
+            }
+        }
+    }
+}
+
+// LDS planes: T fp32 values, aligned, forwards or reversed.
+template <int T>
+__device__ __forceinline__ void put_run(float* p, const float (&v)[T], bool rev) {
+#pragma unroll
+    for (int q = 0; q < T / 4; ++q) {
+        const float4 f = rev ? make_float4(v[T - 1 - 4 * q], v[T - 2 - 4 * q], v[T - 3 - 4 * q],
+                                           v[T - 4 - 4 * q])
+                             : make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        *reinterpret_cast<float4*>(p + 4 * q) = f;
+    }
+}
+
+template <int S>
+__device__ __forceinline__ void scan_lanes(float& P, float& H) {
+    if constexpr (S == kWave)
+        wave_scan(P, H);
+    else
+        seg_scan<S>(P, H);
+}
+
+// distance to the end of a tensor (or of a row), kept in 32 bits
+__device__ __forceinline__ int near(int64_t v) {
+    return static_cast<int>(v < (1 << 30) ? v : (1 << 30));
+}
+
+struct RowArgs {
+    const void* u;
+    const void* delta;
+    const float* A;
+    const void* B;
+    const void* C;
+    const float* D;
+    const float* dt_bias;
+    void* y;
+    const void* xt;
+    int batch, K, Dc, N, H, W, softplus;
+    int64_t L;
+    int groups;     // workgroups per (batch, direction), or per batch when fused
+    unsigned n_wg;  // whole grid, 0 when it is not renumbered
+};
+
+template <int S, int T, int NP, typename Tin, typename Tout, int kMode, bool kZoh>
+__global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_scan_rows(
+    const RowArgs g) {
+    constexpr int kCpw = kWave / S;  // sequences (channels) per wave
+    constexpr int kChunk = S * T;
+    extern __shared__ __align__(16) char lds[];
+
+    const int tid = threadIdx.x;
+    const int lane = tid % kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int cw = lane / S, sl = lane % S;
+    const int Dc = g.Dc, N = g.N;
+    const int64_t L = g.L;
+
+    // Workgroup i runs on XCD i % 8 (own L2): each XCD takes a contiguous
+    // range, so the channels that share B and C rows share an L2.
+    int grp, k, b;
+    if (g.n_wg) {
+        const unsigned bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+        const unsigned per = g.n_wg / 8, rem = g.n_wg % 8, xcd = bid % 8, slot = bid / 8;
+        unsigned id = xcd * per + (xcd < rem ? xcd : rem) + slot;
+        grp = static_cast<int>(id % static_cast<unsigned>(g.groups));
+        id /= static_cast<unsigned>(g.groups);
+        k = static_cast<int>(id % gridDim.y);
+        b = static_cast<int>(id / gridDim.y);
+    } else {
+        grp = blockIdx.x;
+        k = blockIdx.y;
+        b = blockIdx.z;
+    }
+    if constexpr (kMode == kFused) k = wv;  // gridDim.y is 1
+    const int d0 = kMode == kFused ? grp * kCpw : (grp * kRowWaves + wv) * kCpw;
+    if (kMode != kFused && d0 >= Dc) return;
+    const int nc = Dc - d0 < kCpw ? Dc - d0 : kCpw;   // channels of this wave
+    const int cc = cw < nc ? cw : nc - 1;             // slots past them repeat the last, unstored
+    const int64_t bk = static_cast<int64_t>(b) * g.K + k;
+    const int c = k * Dc + d0 + cc;
+    const int iL = kMode == kSeq ? 0 : static_cast<int>(L);  // 2-D maps: L = H * W fits an int
+
+    // fused: LDS planes (rows of Lp elements): input in both scan orders,
+    // then the four directions' outputs
+    const int Lp = kMode == kFused ? (iL + T - 1) / T * T : 0;
+    Tin* u_rows = reinterpret_cast<Tin*>(lds);
+    Tin* u_cols = u_rows + kCpw * Lp;
+    float* y_planes = reinterpret_cast<float*>(u_cols + kCpw * Lp);
+    const bool rev = kMode == kFused && k >= 2;
+    const int lead = rev ? Lp - iL : 0;  // identity positions ahead of the sequence
+
+    const int64_t rows = static_cast<int64_t>(g.batch) * g.K;
+    const int64_t row0 = (bk * Dc + d0) * L;  // first channel's delta row
+    const Tin* delta = static_cast<const Tin*>(g.delta);
+    const Tin* Bm = static_cast<const Tin*>(g.B);
+    const Tin* Cm = static_cast<const Tin*>(g.C);
+    const float bias = g.dt_bias ? g.dt_bias[c] : 0.0f;
+    const float dskip = g.D ? g.D[c] : 0.0f;
+    const bool sp = g.softplus != 0;
+    const float* Ac = g.A + static_cast<size_t>(c) * N;
+
+    // one chunk's run of delta: base at the chunk, lane offsets in 32 bits
+    const int loff = (kCpw > 1 ? cc * static_cast<int>(L) : 0) + sl * T - lead;
+    auto load_row = [&](const Tin* base, int64_t c0, Run<Tin, T>& r) {
+        const int row_first = kCpw > 1 ? cc * static_cast<int>(L) : -near(c0);
+        const int row_last = kCpw > 1 ? row_first + static_cast<int>(L) - 1 : near(L - 1 - c0);
+        load_run<Tin, T>(base + row0 + c0, loff, -near(row0 + c0),
+                         near(rows * Dc * L - row0 - c0), row_first, row_last, r);
+    };
+    auto load_delta = [&](int64_t c0, Run<Tin, T>& r) { load_row(delta, c0, r); };
+    auto load_state = [&](const Tin* base, int64_t c0, int n, Run<Tin, T>& r) {
+        const int64_t at = (bk * N + n) * L + c0;
+        load_run<Tin, T>(base + at, sl * T - lead, -near(at), near(rows * N * L - at), -near(c0),
+                         near(L - 1 - c0), r);
+    };
+    // u of a chunk from global memory: the sequence's own row, or (kMapRows)
+    // the plane read in direction k's order
+    auto load_u = [&](int64_t c0, Run<Tin, T>& r, bool& reversed) {
+        reversed = false;
+        const Tin* u = static_cast<const Tin*>(g.u);
+        if constexpr (kMode == kSeq) {
+            load_row(u, c0, r);
+        } else {
+            const Tin* src = (k & 1) && g.xt ? static_cast<const Tin*>(g.xt) : u;
+            const int64_t p0 = (static_cast<int64_t>(b) * Dc + d0) * L;
+            const int64_t t0 = c0 + sl * T;
+            if (!(k & 1) || g.xt) {
+                reversed = k >= 2;
+                const int64_t at = p0 + (reversed ? L - c0 : c0);
+                load_run<Tin, T>(src + at, reversed ? -T - sl * T : sl * T, -near(at),
+                                 near(static_cast<int64_t>(g.batch) * Dc * L - at),
+                                 reversed ? -near(L - c0) : -near(c0),
+                                 reversed ? near(c0) - 1 : near(L - 1 - c0), r);
+            } else {
+                // column-major gather; positions past the end read the last pixel
+                Tin e[T];
+                const int ts = t0 < L ? static_cast<int>(t0) : iL - 1;
+                const int tt = k >= 2 ? iL - 1 - ts : ts;
+                int w = tt / g.H, h = tt - w * g.H;
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    e[i] = src[p0 + static_cast<int64_t>(h) * g.W + w];
+                    if (t0 + i + 1 < L) {
+                        if (k < 2) {
+                            if (++h == g.H) { h = 0; ++w; }
+                        } else {
+                            if (--h < 0) { h = g.H - 1; --w; }
+                        }
+                    }
+                }
+                __builtin_memcpy(&r, e, sizeof(r));
+            }
+        }
+    };
+
+    Run<Tin, T> draw;
+    load_delta(0, draw);
+    Run<Tin, T> uraw;
+    bool urev = false;
+    if constexpr (kMode != kFused) load_u(0, uraw, urev);
+
+    Run<Tin, T> braw[NP], craw[NP];
+    float araw[NP];
+    auto load_states = [&](int64_t c0, int n) {
+#pragma unroll
+        for (int s = 0; s < NP; ++s) {
+            load_state(Bm, c0, n + s, braw[s]);
+            load_state(Cm, c0, n + s, craw[s]);
+            araw[s] = Ac[n + s];
+        }
+    };
+    load_states(0, 0);
+
+    if constexpr (kMode == kFused) {
+        // the channels' planes, contiguous in x, into both scan orders
+        const int H = g.H, W = g.W;
+        const Tin* x = static_cast<const Tin*>(g.u) + (static_cast<size_t>(b) * Dc + d0) * iL;
+        constexpr int kPer = 16 / static_cast<int>(sizeof(Tin));
+        const int n_el = nc * iL;
+        if (iL % kPer == 0) {
+            for (int e0 = tid * kPer; e0 < n_el; e0 += kRowThreads * kPer) {
+                Tin v[kPer];
+                __builtin_memcpy(v, __builtin_assume_aligned(x + e0, 16), 16);
+                const int ch = kCpw > 1 ? e0 / iL : 0;  // kPer divides L: one plane per vector
+                const int p = e0 - ch * iL;
+                __builtin_memcpy(__builtin_assume_aligned(u_rows + ch * Lp + p, 16), v, 16);
+                int h = p / W, w = p - h * W;
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    u_cols[ch * Lp + w * H + h] = v[i];
+                    if (++w == W) { w = 0; ++h; }
+                }
+            }
+        } else {
+            for (int e0 = tid; e0 < n_el; e0 += 4 * kRowThreads) {
+                Tin v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int e = e0 + j * kRowThreads;
+                    v[j] = x[e < n_el ? e : n_el - 1];
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int e = e0 + j * kRowThreads;
+                    if (e < n_el) {
+                        const int ch = kCpw > 1 ? e / iL : 0;
+                        const int p = e - ch * iL;
+                        const int h = p / W, w = p - h * W;
+                        u_rows[ch * Lp + p] = v[j];
+                        u_cols[ch * Lp + w * H + h] = v[j];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const Tin* u_plane = ((k & 1) ? u_cols : u_rows) + cc * Lp;
+    float* y_plane = y_planes + (k * kCpw + cw) * Lp;
+
+    float carry = 0.0f;  // lane n: state n leaving the previous chunk
+    for (int64_t c0 = 0; c0 < L + lead; c0 += kChunk) {
+        // 1. per-position products of the run
+        float uv[T];
+        int at = 0;  // fused: the run's first element in its plane
+        bool in_plane = true;
+        if constexpr (kMode == kFused) {
+            const int t0 = static_cast<int>(c0) + sl * T;
+            at = rev ? Lp - T - t0 : t0;
+            in_plane = at >= 0 && at < Lp;
+            Run<Tin, T> r;
+            __builtin_memcpy(&r, __builtin_assume_aligned(u_plane + (in_plane ? at : 0),
+                                                          sizeof(Tin) * T < 16 ? 8 : 16),
+                             sizeof(r));
+#pragma unroll
+            for (int i = 0; i < T; ++i) uv[i] = rev ? run_at(r, T - 1 - i) : run_at(r, i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < T; ++i) uv[i] = urev ? run_at(uraw, T - 1 - i) : run_at(uraw, i);
+        }
+        float dl2[T], du[T], yv[T];
+        float s2 = 0.0f;
+#pragma unroll
+        for (int i = 0; i < T; ++i) dl2[i] = run_at(draw, i) + bias;
+        if (sp) {
+#pragma unroll
+            for (int i = 0; i < T; ++i) dl2[i] = softplus(dl2[i]);
+        }
+        const bool first = kMode == kFused && lead > 0 && c0 == 0 && sl == 0;
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            if constexpr (kMode == kFused) {
+                // identity positions ahead of a reversed sequence
+                if (first && i < lead) {
+                    dl2[i] = 0.0f;
+                    uv[i] = 0.0f;
+                }
+            }
+            du[i] = dl2[i] * uv[i];
+            dl2[i] *= kLog2e;
+            yv[i] = dskip * uv[i];
+            s2 += dl2[i];
+        }
+        // 2. the next chunk's delta (and u) in flight during the states
+        const bool more = c0 + kChunk < L + lead;
+        if (more) {
+            load_delta(c0 + kChunk, draw);
+            if constexpr (kMode != kFused) load_u(c0 + kChunk, uraw, urev);
+        }
+        // 3. the states, NP at a time
+#pragma unroll 1
+        for (int n = 0; n < N; n += NP) {
+            float an[NP], a[NP][T], bu[NP][T], cv[NP][T], P[NP], Hs[NP];
+#pragma unroll
+            for (int s = 0; s < NP; ++s) {
+                an[s] = araw[s];
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    bu[s][i] = run_at(braw[s], i);
+                    cv[s][i] = run_at(craw[s], i);
+                    if constexpr (kMode == kFused)
+                        if (first && i < lead) bu[s][i] = 0.0f;
+                }
+            }
+            if (n + NP < N)
+                load_states(c0, n + NP);
+            else if (more)
+                load_states(c0 + kChunk, 0);
+#pragma unroll
+            for (int s = 0; s < NP; ++s) {
+                const float inv_a = kZoh ? 1.0f / an[s] : 0.0f;
+                float agg = 0.0f;
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    const float x2 = dl2[i] * an[s];
+                    a[s][i] = fast_exp2(x2);
+                    const float q = kZoh ? zoh_q(x2, a[s][i], du[i], uv[i], inv_a) : du[i];
+                    bu[s][i] *= q;
+                    agg = i == 0 ? bu[s][0] : __builtin_fmaf(a[s][i], agg, bu[s][i]);
+                }
+                P[s] = fast_exp2(s2 * an[s]);
+                Hs[s] = agg;
+            }
+            if constexpr (NP == 2 && S == kWave) {
+                wave_scan2(P[0], Hs[0], P[1], Hs[1]);
+            } else {
+#pragma unroll
+                for (int s = 0; s < NP; ++s) scan_lanes<S>(P[s], Hs[s]);
+            }
+#pragma unroll
+            for (int s = 0; s < NP; ++s) {
+                float h;
+                if constexpr (S == kWave) {
+                    const float cin = lane_value(carry, n + s);
+                    const float out = __builtin_fmaf(P[s], cin, Hs[s]);
+                    h = shr1(cin, out);  // lane 0 keeps the chunk's carry
+                    carry = lane == n + s ? lane_value(out, kWave - 1) : carry;
+                } else {
+                    const float in = shr1(0.0f, Hs[s]);
+                    h = sl == 0 ? 0.0f : in;
+                }
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    h = __builtin_fmaf(a[s][i], h, bu[s][i]);
+                    yv[i] = __builtin_fmaf(cv[s][i], h, yv[i]);
+                }
+            }
+        }
+        // 4. outputs
+        if constexpr (kMode == kFused) {
+            if (in_plane) put_run<T>(y_plane + at, yv, rev);
+        } else if (cw < nc) {
+            const int left = near(L - c0);
+            Tout* yrow = static_cast<Tout*>(g.y) + row0 + c0 + loff;
+            Tout o[T];
+#pragma unroll
+            for (int i = 0; i < T; ++i) o[i] = from_f32<Tout>(yv[i]);
+            if (sl * T + T <= left) {
+                __builtin_memcpy(yrow, o, sizeof(o));
+            } else {
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+                    if (sl * T + i < left) yrow[i] = o[i];
+            }
+        }
+    }
+
+    if constexpr (kMode == kFused) {
+        __syncthreads();
+        const int H = g.H, W = g.W;
+        Tout* out = static_cast<Tout*>(g.y) + (static_cast<size_t>(b) * Dc + d0) * iL;
+        const int n_el = nc * iL;
+        const int ps = kCpw * Lp;  // one direction's planes
+        for (int e = tid; e < n_el; e += kRowThreads) {
+            const int ch = kCpw > 1 ? e / iL : 0;
+            const int p = e - ch * iL;
+            const int h = p / W, w = p - h * W;
+            const float* yr = y_planes + ch * Lp + p;
+            const float* yc = y_planes + ch * Lp + w * H + h;
+            out[e] = from_f32<Tout>((yr[0] + yr[2 * ps]) + (yc[ps] + yc[3 * ps]));
+        }
+    }
+}
+
+// ------------------------------------------------------------------ launch
+
+// Largest LDS a fused workgroup takes.
+constexpr size_t kFusedLds = 160 * 1024;
+
+inline int row_len(int64_t L, int T) { return static_cast<int>((L + T - 1) / T * T); }
+
+size_t fused_lds(int64_t L, int cpw, int T, size_t in_size) {
+    return static_cast<size_t>(cpw) * row_len(L, T) * (2 * in_size + 4 * sizeof(float));
+}
+
+template <int S, int T, int NP, typename Tin, typename Tout, int kMode, bool kZoh>
+vmb_status launch_rows(const ScanArgs& a, void* y, const void* xt) {
+    constexpr int kCpw = kWave / S;
+    const int64_t per = kMode == kFused ? kCpw : kCpw * kRowWaves;
+    const int64_t groups = (a.channels + per - 1) / per;
+    if (groups > 0x7fffffffLL) return VMB_ERR_UNSUPPORTED;
+    const int64_t gy = kMode == kFused ? 1 : a.K;
+    const int64_t n_wg = groups * gy * a.batch;
+    RowArgs g{a.u, a.delta, a.A, a.B, a.C, a.D, a.dt_bias, y, xt,
+              int(a.batch), int(a.K), int(a.channels), int(a.N), int(a.H), int(a.W), a.softplus,
+              a.L, int(groups), n_wg <= 0x7fffffffLL ? static_cast<unsigned>(n_wg) : 0u};
+    const size_t lds = kMode == kFused ? fused_lds(a.L, kCpw, T, sizeof(Tin)) : 0;
+    const dim3 grid(static_cast<unsigned>(groups), static_cast<unsigned>(gy),
+                    static_cast<unsigned>(a.batch));
+    hipLaunchKernelGGL((k_full_scan_rows<S, T, NP, Tin, Tout, kMode, kZoh>), grid,
+                       dim3(kRowThreads), lds, a.stream, g);
+    return check_launch();
+}
+
+template <int S, int T, typename Tin, typename Tout, int kMode>
+vmb_status launch_np(const ScanArgs& a, void* y, const void* xt) {
+    const bool zoh = (a.options & VMB_SCAN_ZOH) != 0;
+    if (a.N == 1)
+        return zoh ? launch_rows<S, T, 1, Tin, Tout, kMode, true>(a, y, xt)
+                   : launch_rows<S, T, 1, Tin, Tout, kMode, false>(a, y, xt);
+    return zoh ? launch_rows<S, T, 2, Tin, Tout, kMode, true>(a, y, xt)
+               : launch_rows<S, T, 2, Tin, Tout, kMode, false>(a, y, xt);
+}
+
+// Segment and run length: the shortest pass that holds the sequence (16 lanes
+// x 4 positions, 16 x 8, 32 x 8), else a whole wave walking chunks of 512.
+template <typename Tin, typename Tout, int kMode>
+vmb_status launch_shape(const ScanArgs& a, void* y, const void* xt) {
+    if (a.L <= 64) return launch_np<16, 4, Tin, Tout, kMode>(a, y, xt);
+    if (a.L <= 128) return launch_np<16, 8, Tin, Tout, kMode>(a, y, xt);
+    if (a.L <= 256) return launch_np<32, 8, Tin, Tout, kMode>(a, y, xt);
+    return launch_np<64, 8, Tin, Tout, kMode>(a, y, xt);
+}
+
+bool fused_fits(const ScanArgs& a) {
+    const size_t in = a.in_dt == VMB_F32 ? 4 : 2;
+    return a.L <= 16384 && fused_lds(a.L, 1, 8, in) <= kFusedLds;
+}
+
+template <typename Tin, typename Tout>
+vmb_status dispatch(const ScanArgs& a) {
+    if (a.layout == VMB_LAYOUT_SEQ) return launch_shape<Tin, Tout, kSeq>(a, a.y, nullptr);
+    if (fused_fits(a)) return launch_shape<Tin, Tout, kFused>(a, a.y, nullptr);
+    // planes beyond LDS: per-direction fp32 outputs, then the merge pass; with
+    // N = 16 the workspace also has room for column-major plane copies
+    const void* xt = nullptr;
+    vmb_status st;
+    if (full_ws_has_xt(a.batch, a.K, a.channels, a.L, a.N)) {
+        void* xtw = static_cast<char*>(a.ws) + full_ws_xt_offset(a.batch, a.K, a.channels, a.L);
+        st = launch_transpose_planes(a.u, xtw, a.batch, a.channels, a.H, a.W, a.in_dt, a.stream);
+        if (st != VMB_OK) return st;
+        xt = xtw;
+    }
+    st = launch_np<64, 8, Tin, float, kMapRows>(a, a.ws, xt);
+    if (st != VMB_OK) return st;
+    return launch_cross_merge(a.ws, a.y, a.batch, a.channels, a.H, a.W, VMB_F32, a.out_dt,
+                              a.stream);
+}
+
+}  // namespace
+
+vmb_status launch_full_rows(const ScanArgs& a) {
+    if (a.batch > 65535 || a.K > 65535) return VMB_ERR_UNSUPPORTED;
+    if (a.in_dt == VMB_F32) return dispatch<float, float>(a);
+    if (a.out_dt == VMB_BF16) return dispatch<bf16_t, bf16_t>(a);
+    return dispatch<bf16_t, float>(a);
+}
+
+}  // namespace vmb

@@ -213,6 +213,8 @@ inline bool whole_lines(int64_t L, int size) { return (L * size) % 128 == 0; }
 constexpr int64_t kShortMaxL = 416;
 bool use_short_full(const ScanArgs& a);
 vmb_status launch_full_short(const ScanArgs& a, void* y_seq);
+// One wave per sequence, any N (scan_rows.hip); writes a.y in either layout.
+vmb_status launch_full_rows(const ScanArgs& a);
 // Whether the positions-over-lanes kernel is the better fit for this shape.
 bool use_chunked_full(const ScanArgs& a);
 // Channels over lanes, states over the four waves of a workgroup, positions

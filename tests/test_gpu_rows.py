@@ -1,0 +1,111 @@
+"""Full scan with one wave per sequence (every N but 16, and N = 16 rows of odd
+bf16 length): run, segment and chunk boundaries, channel-slot tails, the fused
+2-D form (planes in LDS, reversed directions whose length is no multiple of a
+run), planes beyond LDS, both types and the zero-order-hold option, against the
+fp64 oracle at the tolerances of the other scans."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_util import BF16_TOL, FP32_TOL, assert_close, log, oracle_seq, run_scan, to_f64
+from paper_2412_16602_amd import vmb
+from test_gpu_scan import merged_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def inputs(b, H, W, c, N, layout, dtype="f32", d_value=0.0):
+    shp = workloads.custom_shape(b, H, W, c, N, dtype, 1000 * H + 10 * W + c + N, True)
+    return workloads.make_inputs(shp, layout, d_value=d_value)
+
+
+# runs of 4 (L <= 64) or 8, segments of 16 (L <= 128) and 32 lanes (L <= 256),
+# chunks of 512
+LENGTHS = [1, 3, 4, 5, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1030]
+
+
+@pytest.mark.parametrize("N", [1, 4])
+@pytest.mark.parametrize("L", LENGTHS)
+def test_lengths(L, N):
+    log(f"rows full L={L} N={N}")
+    inp = inputs(1, 1, L, 5, N, "seq")
+    assert_close(to_f64(run_scan(inp, "full", "seq")), oracle_seq(inp, "full", "seq"), **FP32_TOL,
+                 what=f"rows L={L} N={N}")
+
+
+# four waves a workgroup, 4, 2 or 1 channels a wave
+@pytest.mark.parametrize("L", [49, 100, 200, 600])
+@pytest.mark.parametrize("channels", [1, 2, 7, 16, 17])
+@pytest.mark.parametrize("layout", ["seq", "2d"])
+def test_channel_slot_tails(layout, channels, L):
+    log(f"rows full {layout} L={L} channels={channels}")
+    H, W = {49: (7, 7), 100: (10, 10), 200: (8, 25), 600: (20, 30)}[L]
+    inp = inputs(2, H, W, channels, 2, layout)
+    got = to_f64(run_scan(inp, "full", layout))
+    if layout == "seq":
+        assert_close(got, oracle_seq(inp, "full", "seq"), **FP32_TOL, what=f"L={L} c={channels}")
+    else:
+        ref, scale = merged_oracle(inp, "full")
+        assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                     what=f"2d L={L} c={channels}")
+
+
+# the last two maps do not fit LDS in fp32 (24 bytes a pixel) and bf16 (20)
+MAPS = [(1, 5), (5, 1), (3, 3), (7, 9), (11, 11), (13, 17), (16, 16), (23, 29), (32, 32), (41, 51),
+        (80, 85), (90, 93)]
+
+
+@pytest.mark.parametrize("dtype,out", [("f32", "f32"), ("bf16", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("H,W", MAPS)
+def test_maps(H, W, dtype, out):
+    log(f"rows full 2d {H}x{W} {dtype}->{out}")
+    N = 1 if (H + W) % 4 == 0 else 8
+    inp = inputs(1, H, W, 3, N, "2d", dtype, d_value=1.0)
+    y = run_scan(inp, "full", "2d", out_dtype=torch.bfloat16 if out == "bf16" else torch.float32)
+    ref, scale = merged_oracle(inp, "full")
+    tol = BF16_TOL if out == "bf16" else FP32_TOL
+    assert_close(to_f64(y), ref, rtol=tol["rtol"], atol=4 * tol["atol"], scale=scale,
+                 what=f"2d {H}x{W} {dtype}->{out}")
+
+
+@pytest.mark.parametrize("H,W", [(1, 421), (27, 31), (61, 67), (97, 101)])
+@pytest.mark.parametrize("layout", ["seq", "2d"])
+def test_odd_bf16_rows_n16(layout, H, W):
+    log(f"full {layout} n16 bf16 {H}x{W}")
+    inp = inputs(1, H, W, 5, 16, layout, "bf16", d_value=1.0)
+    got = to_f64(run_scan(inp, "full", layout, out_dtype=torch.float32))
+    if layout == "seq":
+        assert_close(got, oracle_seq(inp, "full", "seq"), **FP32_TOL, what=f"odd {H}x{W}")
+    else:
+        ref, scale = merged_oracle(inp, "full")
+        assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                     what=f"odd 2d {H}x{W}")
+
+
+@pytest.mark.parametrize("N", [1, 8])
+@pytest.mark.parametrize("layout,H,W", [("seq", 1, 530), ("2d", 6, 7), ("2d", 23, 25),
+                                        ("2d", 90, 91)])
+def test_zoh(layout, H, W, N):
+    log(f"rows zoh {layout} {H}x{W} N={N}")
+    inp = inputs(1, H, W, 6, N, layout)
+    got = to_f64(run_scan(inp, "full", layout, options=vmb.VMB_SCAN_ZOH))
+    if layout == "seq":
+        ref = oracle_seq(inp, "full", "seq", options=oracle.ZOH)
+        assert_close(got, ref, **FP32_TOL, what=f"zoh {H}x{W}")
+    else:
+        ref, scale = merged_oracle(inp, "full", options=oracle.ZOH)
+        assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                     what=f"zoh 2d {H}x{W}")
+
+
+def test_no_bias_no_skip_no_softplus():
+    log("rows softplus off")
+    inp = inputs(1, 15, 19, 6, 2, "2d")
+    delta = (np.abs(inp.delta) * 0.05 + 1e-3).astype(np.float32)
+    kw = dict(softplus=False, use_bias=False, use_d=False, delta=delta)
+    got = to_f64(run_scan(inp, "full", "2d", **kw))
+    ref, scale = merged_oracle(inp, "full", **kw)
+    assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                 what="softplus off")
