@@ -11,21 +11,27 @@
 // re-walks its run from the state entering it, accumulating y_i += C_i h_i.
 // The state leaving a chunk is kept per state in lane n of one register.
 //
-// What bounds it: with few states the timescale's softplus (2 of its about 15
-// instructions at quarter rate), the products and the bytes of delta and y,
-// not the recurrence; so delta, B and C are read as whole 16-byte vectors of
-// a run, the next state's B and C (and the next chunk's delta) in flight
-// while the current ones are in use.
+// What bounds it: instruction issue (32 x 56x56, 192 channels, bf16, sequence
+// layout: 250 cycles a SIMD per 64 positions at N = 1, of which softplus is
+// about 45, and 46 more per state), near the rate of a copy in fp32 (4.1 TB/s).
+// delta, B and C are read as whole 16-byte vectors of a run, the next state's
+// B and C (and the next chunk's delta) in flight while the current ones are in
+// use: their values are unpacked before those loads are issued (pin), or the
+// loop would wait for them at the end of the step that issued them.
+// At the same shape, 2-D: one lane per channel 1822 us; this kernel 122 us (176
+// with an output plane per direction, two workgroups a CU instead of four,
+// and the early wait).
 //
 // 2-D layout, planes that fit LDS (kFused): a workgroup owns a channel (2 or
 // 4 short ones) with one wave per direction. The input plane is copied into
-// LDS in both scan orders and each direction leaves its outputs there as a
-// plane of its own; after a barrier the four are summed in the association of
-// the cross-merge, (y0 + y2) + (y1 + y3), and stored. Per-direction outputs
-// never reach memory (the merge pass it replaces moved 32 bytes per pixel and
-// channel). All LDS runs are aligned vectors: the reversed directions start
-// their runs at the padded end of the plane, with identity positions
-// (Delta = 0, B = 0) ahead of the first pixel.
+// LDS in both scan orders, and each order has one output plane, which its
+// forward and its reversed direction share (see step 4); at the end the two
+// are summed and stored, in the association of the cross-merge,
+// (y0 + y2) + (y1 + y3). Per-direction outputs never reach memory (the merge
+// pass it replaces moved 32 bytes per pixel and channel). All LDS runs are
+// aligned vectors: the reversed directions start their runs at the padded end
+// of the plane, with identity positions (Delta = 0, B = 0) ahead of the first
+// pixel.
 #include "vmb_internal.h"
 
 namespace vmb {
@@ -101,14 +107,25 @@ __device__ __forceinline__ void load_run(const Tin* base, int off, int lo, int h
 
 // LDS planes: T fp32 values, aligned, forwards or reversed.
 template <int T>
-__device__ __forceinline__ void put_run(float* p, const float (&v)[T], bool rev) {
+__device__ __forceinline__ void put_run(float* p, const float (&v)[T], bool rev, bool add) {
+    float4 f[T / 4];
 #pragma unroll
-    for (int q = 0; q < T / 4; ++q) {
-        const float4 f = rev ? make_float4(v[T - 1 - 4 * q], v[T - 2 - 4 * q], v[T - 3 - 4 * q],
-                                           v[T - 4 - 4 * q])
-                             : make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        *reinterpret_cast<float4*>(p + 4 * q) = f;
+    for (int q = 0; q < T / 4; ++q)
+        f[q] = rev ? make_float4(v[T - 1 - 4 * q], v[T - 2 - 4 * q], v[T - 3 - 4 * q],
+                                 v[T - 4 - 4 * q])
+                   : make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    if (add) {
+#pragma unroll
+        for (int q = 0; q < T / 4; ++q) {
+            const float4 o = *reinterpret_cast<const float4*>(p + 4 * q);
+            f[q].x += o.x;
+            f[q].y += o.y;
+            f[q].z += o.z;
+            f[q].w += o.w;
+        }
     }
+#pragma unroll
+    for (int q = 0; q < T / 4; ++q) *reinterpret_cast<float4*>(p + 4 * q) = f[q];
 }
 
 template <int S>
@@ -119,9 +136,24 @@ __device__ __forceinline__ void scan_lanes(float& P, float& H) {
         seg_scan<S>(P, H);
 }
 
-// distance to the end of a tensor (or of a row), kept in 32 bits
+// distance (>= 0) to the end of a tensor or of a row, kept in 32 bits
 __device__ __forceinline__ int near(int64_t v) {
-    return static_cast<int>(v < (1 << 30) ? v : (1 << 30));
+    return (static_cast<uint64_t>(v) >> 30) ? (1 << 30) : static_cast<int>(v);
+}
+
+// values formed here and not sunk past the loads that follow
+template <int T>
+__device__ __forceinline__ void pin(float (&v)[T]) {
+#pragma unroll
+    for (int i = 0; i < T; ++i) asm volatile("" : "+v"(v[i]));
+}
+
+// smallest number of waves per SIMD the registers are budgeted for: what the
+// fused form's LDS admits at 56x56 (12 or 16 bytes a pixel), and the same
+// budget elsewhere (two fp32 states at a time need about 150 registers)
+template <typename Tin, int NP>
+constexpr int row_waves() {
+    return sizeof(Tin) == 4 && NP == 2 ? 3 : 4;
 }
 
 struct RowArgs {
@@ -141,7 +173,7 @@ struct RowArgs {
 };
 
 template <int S, int T, int NP, typename Tin, typename Tout, int kMode, bool kZoh>
-__global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_scan_rows(
+__global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_scan_rows(
     const RowArgs g) {
     constexpr int kCpw = kWave / S;  // sequences (channels) per wave
     constexpr int kChunk = S * T;
@@ -151,7 +183,7 @@ __global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_s
     const int lane = tid % kWave;
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int cw = lane / S, sl = lane % S;
-    const int Dc = g.Dc, N = g.N;
+    const int Dc = g.Dc, N = NP == 1 ? 1 : g.N;  // N is 1 or even
     const int64_t L = g.L;
 
     // Workgroup i runs on XCD i % 8 (own L2): each XCD takes a contiguous
@@ -180,7 +212,7 @@ __global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_s
     const int iL = kMode == kSeq ? 0 : static_cast<int>(L);  // 2-D maps: L = H * W fits an int
 
     // fused: LDS planes (rows of Lp elements): input in both scan orders,
-    // then the four directions' outputs
+    // then the outputs of both
     const int Lp = kMode == kFused ? (iL + T - 1) / T * T : 0;
     Tin* u_rows = reinterpret_cast<Tin*>(lds);
     Tin* u_cols = u_rows + kCpw * Lp;
@@ -271,50 +303,45 @@ __global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_s
     load_states(0, 0);
 
     if constexpr (kMode == kFused) {
-        // the channels' planes, contiguous in x, into both scan orders
-        const int H = g.H, W = g.W;
-        const Tin* x = static_cast<const Tin*>(g.u) + (static_cast<size_t>(b) * Dc + d0) * iL;
+        // the channels' planes into both scan orders, vectors of kPer pixels
         constexpr int kPer = 16 / static_cast<int>(sizeof(Tin));
-        const int n_el = nc * iL;
-        if (iL % kPer == 0) {
-            for (int e0 = tid * kPer; e0 < n_el; e0 += kRowThreads * kPer) {
-                Tin v[kPer];
-                __builtin_memcpy(v, __builtin_assume_aligned(x + e0, 16), 16);
-                const int ch = kCpw > 1 ? e0 / iL : 0;  // kPer divides L: one plane per vector
-                const int p = e0 - ch * iL;
-                __builtin_memcpy(__builtin_assume_aligned(u_rows + ch * Lp + p, 16), v, 16);
-                int h = p / W, w = p - h * W;
+        constexpr int kThr = kRowThreads / kCpw;  // threads per plane
+        static_assert(kCpw == 1 || kThr * 4 >= S * T, "one pass over short planes");
+        const int ch = tid / kThr;
+        const Tin* x = static_cast<const Tin*>(g.u) +
+                       (static_cast<size_t>(b) * Dc + d0 + (ch < nc ? ch : 0)) * iL;
+        Tin* pr = u_rows + ch * Lp;
+        Tin* pc = u_cols + ch * Lp;
+        for (int p = (tid % kThr) * kPer; p < iL; p += kThr * kPer) {
+            Tin v[kPer];
+            const int n = iL - p < kPer ? iL - p : kPer;
+            int h = p / g.W, w = p - h * g.W;
+            if (n == kPer) {
+                __builtin_memcpy(v, x + p, 16);
+                __builtin_memcpy(__builtin_assume_aligned(pr + p, T == 4 ? 8 : 16), v, 16);
 #pragma unroll
                 for (int i = 0; i < kPer; ++i) {
-                    u_cols[ch * Lp + w * H + h] = v[i];
-                    if (++w == W) { w = 0; ++h; }
+                    pc[w * g.H + h] = v[i];
+                    if (++w == g.W) { w = 0; ++h; }
                 }
-            }
-        } else {
-            for (int e0 = tid; e0 < n_el; e0 += 4 * kRowThreads) {
-                Tin v[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int e = e0 + j * kRowThreads;
-                    v[j] = x[e < n_el ? e : n_el - 1];
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int e = e0 + j * kRowThreads;
-                    if (e < n_el) {
-                        const int ch = kCpw > 1 ? e / iL : 0;
-                        const int p = e - ch * iL;
-                        const int h = p / W, w = p - h * W;
-                        u_rows[ch * Lp + p] = v[j];
-                        u_cols[ch * Lp + w * H + h] = v[j];
-                    }
+            } else {
+#pragma unroll 1
+                for (int i = 0; i < n; ++i) {
+                    const Tin e = x[p + i];
+                    pr[p + i] = e;
+                    pc[w * g.H + h] = e;
+                    if (++w == g.W) { w = 0; ++h; }
                 }
             }
         }
         __syncthreads();
     }
     const Tin* u_plane = ((k & 1) ? u_cols : u_rows) + cc * Lp;
-    float* y_plane = y_planes + (k * kCpw + cw) * Lp;
+    float* y_plane = y_planes + ((k & 1) * kCpw + cw) * Lp;
+    // the middle chunk, around which the two directions of a plane exchange
+    // (kFused, step 4)
+    const int chunks = kMode == kFused ? (Lp + kChunk - 1) / kChunk : 0;
+    const int64_t middle = kMode == kFused ? static_cast<int64_t>((chunks - 1) / 2) * kChunk : -1;
 
     float carry = 0.0f;  // lane n: state n leaving the previous chunk
     for (int64_t c0 = 0; c0 < L + lead; c0 += kChunk) {
@@ -344,21 +371,23 @@ __global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_s
 #pragma unroll
             for (int i = 0; i < T; ++i) dl2[i] = softplus(dl2[i]);
         }
-        const bool first = kMode == kFused && lead > 0 && c0 == 0 && sl == 0;
+        const bool led = kMode == kFused && lead > 0 && c0 == 0;
+        if (led) {  // identity positions ahead of a reversed sequence
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                if (sl == 0 && i < lead) dl2[i] = uv[i] = 0.0f;
+                asm volatile("" : "+v"(dl2[i]), "+v"(uv[i]));  // a branch of its own
+            }
+        }
 #pragma unroll
         for (int i = 0; i < T; ++i) {
-            if constexpr (kMode == kFused) {
-                // identity positions ahead of a reversed sequence
-                if (first && i < lead) {
-                    dl2[i] = 0.0f;
-                    uv[i] = 0.0f;
-                }
-            }
             du[i] = dl2[i] * uv[i];
             dl2[i] *= kLog2e;
             yv[i] = dskip * uv[i];
             s2 += dl2[i];
         }
+        // the loads below reuse the raw registers
+        pin(dl2), pin(du), pin(yv);
         // 2. the next chunk's delta (and u) in flight during the states
         const bool more = c0 + kChunk < L + lead;
         if (more) {
@@ -376,8 +405,16 @@ __global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_s
                 for (int i = 0; i < T; ++i) {
                     bu[s][i] = run_at(braw[s], i);
                     cv[s][i] = run_at(craw[s], i);
-                    if constexpr (kMode == kFused)
-                        if (first && i < lead) bu[s][i] = 0.0f;
+                }
+                // the loads below reuse the raw registers
+                pin(bu[s]), pin(cv[s]);
+                asm volatile("" : "+v"(an[s]));
+                if (led) {
+#pragma unroll
+                    for (int i = 0; i < T; ++i) {
+                        if (sl == 0 && i < lead) bu[s][i] = 0.0f;
+                        asm volatile("" : "+v"(bu[s][i]));
+                    }
                 }
             }
             if (n + NP < N)
@@ -426,7 +463,21 @@ __global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_s
         }
         // 4. outputs
         if constexpr (kMode == kFused) {
-            if (in_plane) put_run<T>(y_plane + at, yv, rev);
+            // A plane takes the forward and the reversed direction of its
+            // scan order: whichever reaches a run first (in chunks; the
+            // forward one on a tie) stores it, the other adds to it, so the
+            // sum is the same whatever the waves' timing. Runs reached in
+            // different chunks are reached on different sides of the middle
+            // one, so only that chunk needs barriers: before it, between the
+            // forward and the reversed waves, and after it.
+            const int other = (rev ? at : Lp - T - at) / kChunk;
+            const int mine = static_cast<int>(c0 / kChunk);
+            const bool add = in_plane && (rev ? other <= mine : other < mine);
+            if (c0 == middle) __syncthreads();
+            if (!rev && in_plane) put_run<T>(y_plane + at, yv, false, add);
+            if (c0 == middle) __syncthreads();
+            if (rev && in_plane) put_run<T>(y_plane + at, yv, true, add);
+            if (c0 == middle) __syncthreads();
         } else if (cw < nc) {
             const int left = near(L - c0);
             Tout* yrow = static_cast<Tout*>(g.y) + row0 + c0 + loff;
@@ -446,16 +497,35 @@ __global__ __launch_bounds__(kRowThreads, kMode == kFused ? 2 : 3) void k_full_s
     if constexpr (kMode == kFused) {
         __syncthreads();
         const int H = g.H, W = g.W;
-        Tout* out = static_cast<Tout*>(g.y) + (static_cast<size_t>(b) * Dc + d0) * iL;
-        const int n_el = nc * iL;
-        const int ps = kCpw * Lp;  // one direction's planes
-        for (int e = tid; e < n_el; e += kRowThreads) {
-            const int ch = kCpw > 1 ? e / iL : 0;
-            const int p = e - ch * iL;
-            const int h = p / W, w = p - h * W;
-            const float* yr = y_planes + ch * Lp + p;
-            const float* yc = y_planes + ch * Lp + w * H + h;
-            out[e] = from_f32<Tout>((yr[0] + yr[2 * ps]) + (yc[ps] + yc[3 * ps]));
+        constexpr int kThr = kRowThreads / kCpw;  // threads per plane, 4 pixels each
+        const int ch = tid / kThr;
+        if (ch >= nc) return;
+        Tout* out = static_cast<Tout*>(g.y) + (static_cast<size_t>(b) * Dc + d0 + ch) * iL;
+        const float* yr = y_planes + ch * Lp;
+        const float* yc = y_planes + (kCpw + ch) * Lp;
+        int p = (tid % kThr) * 4;
+        int h = p / W, w = p - h * W;
+        const int dh = 4 * kThr / W, dw = 4 * kThr - dh * W;
+        for (; p < iL; p += 4 * kThr) {
+            const float4 r = *reinterpret_cast<const float4*>(yr + p);  // whole runs: Lp % 4 == 0
+            const float rv[4] = {r.x, r.y, r.z, r.w};
+            Tout o[4];
+            int hh = h, ww = w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                o[i] = from_f32<Tout>(rv[i] + yc[p + i < iL ? ww * H + hh : 0]);
+                if (++ww == W) { ww = 0; ++hh; }
+            }
+            if (p + 4 <= iL) {
+                __builtin_memcpy(out + p, o, sizeof(o));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (p + i < iL) out[p + i] = o[i];
+            }
+            w += dw;
+            h += dh;
+            if (w >= W) { w -= W; ++h; }
         }
     }
 }
@@ -468,7 +538,7 @@ constexpr size_t kFusedLds = 160 * 1024;
 inline int row_len(int64_t L, int T) { return static_cast<int>((L + T - 1) / T * T); }
 
 size_t fused_lds(int64_t L, int cpw, int T, size_t in_size) {
-    return static_cast<size_t>(cpw) * row_len(L, T) * (2 * in_size + 4 * sizeof(float));
+    return static_cast<size_t>(cpw) * row_len(L, T) * 2 * (in_size + sizeof(float));
 }
 
 template <int S, int T, int NP, typename Tin, typename Tout, int kMode, bool kZoh>
