@@ -12,376 +12,447 @@
 //                                                        x_dbl[0, t], the broadcast)
 // delta is s_Delta(u): the scan adds the Parameter (dt_bias) and applies softplus.
 //
-// Both products are dense contractions and run on the matrix cores
-// (v_mfma_f32_16x16x4f32, fp32 inputs and accumulation). The weights of a
-// direction are shared by every position of every batch entry, so positions
-// are flattened over (batch, t): a workgroup owns P = 16 CB consecutive
-// flattened positions of one direction (CB = 1, 2 or 4 column blocks of 16,
-// chosen on the host so that the grid fills the chip), and short sequences
-// still fill whole tiles. A tile of 16 or 32 positions reads only part of
-// each 128-byte line of a channel row; its neighbours read the rest. The
-// dispatcher deals workgroups to the eight XCDs (each with its own L2)
-// round-robin, so the 1-D grid is remapped to give each XCD a contiguous
-// range of tiles: neighbours then share one L2 instead of each XCD fetching
-// the line again.
-//   1. x_dbl: the channels are walked in chunks of 64; each chunk of u and of
-//      W is staged in LDS (row strides padded by one word: the MFMA operand
-//      reads are conflict-free) while the next chunk is already being loaded
-//      into registers. The four waves split the work as CB column blocks x
-//      KS = 4 / CB interleaved channel slices; each wave accumulates all
-//      R + 2N rows (MB 16-row blocks) of its column block over its slice, and
-//      the slices are summed through LDS. B and C rows leave from the
-//      accumulators; the R timescale rows go to LDS.
-//      bf16 inputs take the bf16 matrix cores (v_mfma_f32_16x16x16_bf16): u
-//      is exact in bf16, W is split into bf16 hi + lo parts (hi the rounded
-//      W, lo the rounded remainder), and the two products per row block
-//      are exact in fp32, so W is carried to about 2^-17 of itself (far
-//      below the bf16 rounding of the outputs) at eight times the fp32
-//      matrix rate. u is staged transposed ([position][channel]) and W as
-//      [row][channel], so each lane's four consecutive channels are one
-//      8-byte LDS read.
-//   2. delta: W_dt is staged in LDS 64 channels at a time (a contiguous
-//      block); each wave takes one 16-channel row block of the chunk and all
-//      column blocks, K = R in steps of 4.
-// MFMA 16x16x4 operand layout: lane l holds A[l % 16][l / 16] and
-// B[l / 16][l % 16]; result register v of lane l is D[4 (l / 16) + v][l % 16].
+// Both products are dense contractions on the matrix cores. Every wave works
+// on its own, from global memory through registers: a lane loads VP
+// consecutive positions of a channel row as one vector, and element j of it
+// is the operand of column block j, so column c of block j is position
+// VP c + j of the wave's 16 VP positions. That permutation of the positions
+// makes every load and store of a row one contiguous segment of 16 VP
+// elements, needs no transpose and, since a column never mixes with another,
+// no LDS and no barrier. The order in which the contraction runs over the
+// channels is free as well: a lane group takes the channels whose weights are
+// consecutive in memory (one vector load of W).
+//   1. x_dbl: steps of 16 (fp32) or 32 (bf16) channels, the next step's u and
+//      W loads in flight during a step's products. fp32 inputs take
+//      v_mfma_f32_16x16x4f32. bf16 inputs take v_mfma_f32_16x16x32_bf16: u is
+//      exact in bf16, W is split into bf16 hi + lo parts (hi the rounded W, lo
+//      the rounded remainder), and the two products per row block are exact in
+//      fp32, so W is carried to about 2^-17 of itself (far below the bf16
+//      rounding of the outputs).
+//      With KS > 1 the KS waves of a tile take every KS-th step and their sums
+//      meet in LDS, added in wave order.
+//   2. delta: the accumulator of x_dbl row 4 q + v of a block, held by lane
+//      group q, is used as it is as the operand of contraction step v (whose
+//      four indices are then the rows v, 4 + v, 8 + v, 12 + v), against the
+//      four consecutive W_dt[d, 4 q ..] the lane loads as one vector. KS waves
+//      take every KS-th block of 16 channels.
+// What bounds it (32 x 28x28, 384 channels, rank 12, fp32, 308 MB of u and
+// delta): the same tile-wise copy without products takes 72 us (4.3 TB/s; 58 us
+// in linear order) and the products 33 us at the fp32 matrix rate; they
+// overlap only in part, 100 us (127 with u and W staged in LDS behind two
+// barriers per 64 channels, and the low-rank product through LDS). More steps
+// in flight (2 or 3) or three or four waves a SIMD measured no faster.
+// 32 x 14x14, 768 channels, rank 24, bf16: 103 -> 39 us; 128 x 56x56, 192
+// channels, rank 6, bf16: 527 -> 313 us.
+// Positions are taken in groups of VP per sequence; the last group of a
+// sequence starts at L - VP and forms the positions it shares with the group
+// before a second time, to the same bits. 16x16 accumulators: register v of
+// lane l is row 4 (l / 16) + v, column l % 16.
+//
+// The dispatcher deals workgroups to the eight XCDs (each with its own L2)
+// round-robin; the 1-D grid is renumbered to give each XCD a contiguous range
+// of tiles, so tiles that share a cache line or the weights share an L2.
+#include <type_traits>
+
 #include "vmb_internal.h"
 
 namespace vmb {
 namespace {
 
-constexpr int kDC = 64;           // channels per staged chunk
-constexpr int kPadD = kDC + 1;    // LDS row stride of the W chunk
-constexpr int kMaxMB = 6;         // 16-row blocks of x_dbl at most (R <= 64, N <= 16)
-constexpr int kMaxR = 64;         // timescale rank at most
-constexpr int kPadR = kMaxR + 1;  // LDS row stride of the W_dt chunk
+constexpr int kMaxMB = 6;  // 16-row blocks of x_dbl at most (R <= 64, N <= 16)
+constexpr int kMaxR = 64;  // timescale rank at most
+constexpr int kThreads = 256;
+constexpr int kWaves = 4;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-constexpr int kStrideB = kDC + 4;  // bf16 LDS row stride (elements): 8-byte aligned rows
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-
-// D += A B with A 16 x 16 (rows x K) and B 16 x 16 (K x columns) in bf16:
-// lane l holds A[l % 16][4 (l / 16) .. + 3] and B[4 (l / 16) .. + 3][l % 16]
-__device__ __forceinline__ f32x4 mfma16x16x16bf16(s16x4 a, s16x4 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+__device__ __forceinline__ f32x4 mfma16x16x32(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-__device__ __forceinline__ unsigned short bf16_bits(float x) {
-    const bf16_t h = from_f32<bf16_t>(x);
-    return *reinterpret_cast<const unsigned short*>(&h);
-}
-__device__ __forceinline__ float bf16_value(unsigned short b) {
-    return __uint_as_float(static_cast<unsigned>(b) << 16);
+__device__ __forceinline__ uint32_t bf16_bits(float x) { return from_f32<bf16_t>(x).bits; }
+__device__ __forceinline__ float bf16_value(uint32_t b) { return __uint_as_float(b << 16); }
+
+// VP consecutive elements of a row
+template <typename T, int VP>
+struct Vec {
+    T v[VP];
+};
+
+// channels per step and per lane (a lane group holds a quarter of a step)
+template <typename T>
+constexpr int step_channels() {
+    return sizeof(T) == 4 ? 16 : 32;
 }
 
-// an offset the compiler cannot see through: a load at a selected offset
-// stays one unconditional load instead of a branch per arm of the select
-__device__ __forceinline__ size_t opaque(size_t x) {
-    asm("" : "+v"(x));
-    return x;
-}
+// registers of one step: u of the lane's channels and W of all row blocks
+template <typename T, int MB, int VP>
+struct Step {
+    static constexpr int kCh = step_channels<T>() / 4;
+    Vec<T, VP> u[kCh];
+    float w[MB][kCh];
+};
 
-template <typename T, int MB, int CB>
-__global__ __launch_bounds__(256) void k_projections(
+template <typename T, int MB, int VP, int KS>
+__global__ __launch_bounds__(kThreads, 2) void k_projections(
     const T* __restrict__ u, const float* __restrict__ W, const float* __restrict__ Wdt,
     T* __restrict__ delta, T* __restrict__ Bo, T* __restrict__ Co, int K, int Dc, int L, int N,
-    int R, int64_t positions, int tiles) {
-    constexpr int P = 16 * CB;   // positions per workgroup
-    constexpr int PP = P + 1;    // LDS row stride of the u chunk and the timescale rows
-    constexpr int KS = 4 / CB;   // channel slices
-    constexpr bool kBf = sizeof(T) == 2;  // bf16 matrix-core path
-    // staging sizes in floats: fp32 u [channel][position] and W [row][channel];
-    // bf16 u [position][channel] and W hi, lo [row][channel] (2-byte elements)
-    constexpr int kUsz = kBf ? (P * kStrideB) / 2 : kDC * PP;
-    constexpr int kWsz = kBf ? 16 * MB * kStrideB : 16 * MB * kPadD;
-    constexpr int kPool = (kUsz + kWsz) > kDC * kPadR ? (kUsz + kWsz) : kDC * kPadR;
-    static_assert((KS - 1) * CB * MB * 256 <= kPool, "partials fit the staging pool");
-    __shared__ __align__(16) float pool[kPool];  // phase 1: u chunk, W chunk, partials; phase 2: W_dt chunk
-    __shared__ float ss[kMaxR * PP];  // timescale rows x_dbl[0 .. R)
-    float* su = pool;
-    float* sw = pool + kUsz;
-    unsigned short* su16 = reinterpret_cast<unsigned short*>(pool);
-    unsigned short* swh = reinterpret_cast<unsigned short*>(pool + kUsz);
-    unsigned short* swl = swh + 16 * MB * kStrideB;
+    int R, int64_t groups, int tiles) {
+    constexpr int PW = kWaves / KS;  // tiles per workgroup
+    constexpr int kStep = step_channels<T>();
+    constexpr int kCh = kStep / 4;
+    constexpr int NB = 2;            // step buffers: one step in flight
+    constexpr int kRegs = MB * VP;   // accumulators (4 registers each) of a tile
+    __shared__ float part[KS > 1 ? kWaves / 2 * kRegs * 256 : 1];
 
-    // XCD-contiguous tile order: workgroup i runs on XCD i % 8; XCD x takes
-    // tiles [x q + min(x, rem), ...) of the K * tiles in (k, tile) order
     const int nwg = static_cast<int>(gridDim.x), wg = static_cast<int>(blockIdx.x);
-    const int q = nwg / 8, rem = nwg % 8, xcd = wg % 8, idx = wg / 8;
-    const int logical = xcd * q + (xcd < rem ? xcd : rem) + idx;
-    const int k = logical / tiles;
-    const int64_t p0 = static_cast<int64_t>(logical - k * tiles) * P;
+    const int q = nwg / 8, rem = nwg % 8, xcd = wg % 8;
+    const int logical = xcd * q + (xcd < rem ? xcd : rem) + wg / 8;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 15, kq = lane >> 4;  // MFMA operand coordinates
-    const int cb = wv % CB, ks = wv / CB;       // this wave's column block and channel slice
-    const int M = R + 2 * N;                    // (M + 15) / 16 == MB
+    const int pw = wv % PW, ks = wv / PW;
+    const int wgs_k = (tiles + PW - 1) / PW;  // workgroups per direction
+    const int k = logical / wgs_k;
+    const int tile = (logical - k * wgs_k) * PW + pw;
+    if (KS == 1 && tile >= tiles) return;  // KS > 1: PW tiles divide evenly or PW == 1
+    const int col = lane & 15, kq = lane >> 4;
+    const int M = R + 2 * N;  // (M + 15) / 16 == MB
     const size_t l = static_cast<size_t>(L);
-    const float* Wk = W + static_cast<size_t>(k) * M * Dc;
 
-    // offset of flattened position p0 + c in a [batch, K, rows, L] tensor, row 0
-    auto pos_base = [&](int c, int rows, bool& ok) -> size_t {
-        const int64_t p = p0 + c;
-        ok = p < positions;
-        if (!ok) return 0;
-        const int64_t b = p / L, t = p - b * L;
-        return (static_cast<size_t>(b) * K + k) * rows * l + static_cast<size_t>(t);
-    };
-
-    // chunk loaders: u rows over threads with a fixed position per thread,
-    // W rows with a fixed channel per thread
-    constexpr int kURows = 256 / P;  // u rows per pass
-    constexpr int kUL = kDC / kURows;
-    constexpr int kWL = 16 * MB / 4;
-    const int uc = tid % P, ur0 = tid / P;
-    bool uok;
-    const size_t ubase = pos_base(uc, Dc, uok);
-    const int wc = tid & 63, wr0 = tid >> 6;
-    // The loads are unconditional (an element out of range reads element 0
-    // instead) and keep the raw values, so a chunk's loads stay in flight
-    // until its LDS store. For 2-byte inputs the offset is made opaque: a
-    // select between two addresses would otherwise become a branch per arm,
-    // with the conversion (and so a wait) inside each.
-    auto sel = [](size_t x) { return sizeof(T) == 2 ? opaque(x) : x; };
-    T pu[kUL];
-    float pw[kWL];
-    auto u_ok = [&](int d0, int j) { return uok && d0 + ur0 + kURows * j < Dc; };
-    auto w_ok = [&](int d0, int j) { return wr0 + 4 * j < M && d0 + wc < Dc; };
-    auto load = [&](int d0) {
-#pragma unroll
-        for (int j = 0; j < kUL; ++j)
-            pu[j] = u[sel(u_ok(d0, j) ? ubase + static_cast<size_t>(d0 + ur0 + kURows * j) * l
-                                      : 0)];
-#pragma unroll
-        for (int j = 0; j < kWL; ++j)
-            pw[j] = Wk[w_ok(d0, j) ? static_cast<size_t>(wr0 + 4 * j) * Dc + d0 + wc : 0];
-    };
+    // this lane's group of VP positions
+    const int per_seq = (L + VP - 1) / VP;
+    const int64_t gi = static_cast<int64_t>(tile) * 16 + col;
+    const bool ok = gi < groups;
+    const int64_t gc = ok ? gi : groups - 1;
+    const int64_t b = gc / per_seq;
+    const int tg = static_cast<int>(gc - b * per_seq) * VP;
+    const int t0 = tg + VP <= L ? tg : L - VP;
+    const size_t bk = static_cast<size_t>(b) * K + k;
 
     // 1. x_dbl
-    f32x4 acc[MB];
+    const T* up = u + (bk * Dc) * l + t0;  // channel 0
+    const float* Wk = W + static_cast<size_t>(k) * M * Dc;
+    // W row of this lane in each row block (the last block's rows past M repeat one)
+    const int m_last = 16 * (MB - 1) + col;
+    const float* wlane = Wk + static_cast<size_t>(col) * Dc + kq * kCh;
+    const float* wlast = Wk + static_cast<size_t>(m_last < M ? m_last : M - 1) * Dc + kq * kCh;
+    const T* ulane = up + static_cast<size_t>(kq * kCh) * l;
+    auto load = [&](Step<T, MB, VP>& s, int g) {  // a whole step, no branches
+        const size_t c0 = static_cast<size_t>(g) * kStep;
+        const T* p = ulane + c0 * l;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    load(0);
-    for (int d0 = 0; d0 < Dc; d0 += kDC) {
-        __syncthreads();  // the previous chunk has been read
-        if constexpr (kBf) {
+        for (int i = 0; i < kCh; ++i) __builtin_memcpy(&s.u[i], p + i * l, sizeof(s.u[i]));
 #pragma unroll
-            for (int j = 0; j < kUL; ++j)
-                su16[uc * kStrideB + ur0 + kURows * j] =
-                    u_ok(d0, j) ? *reinterpret_cast<const unsigned short*>(&pu[j]) : 0;
+        for (int mb = 0; mb < MB; ++mb)
+            __builtin_memcpy(s.w[mb],
+                             (mb + 1 < MB ? wlane + static_cast<size_t>(16 * mb) * Dc : wlast) + c0,
+                             sizeof(s.w[mb]));
+    };
+    // the last Dc % kStep channels: past the end both operands are 0
+    auto load_tail = [&](Step<T, MB, VP>& s, int g) {
+        const int c0 = g * kStep + kq * kCh;
 #pragma unroll
-            for (int j = 0; j < kWL; ++j) {
-                const float w = w_ok(d0, j) ? pw[j] : 0.0f;
-                const unsigned short hi = bf16_bits(w);
-                swh[(wr0 + 4 * j) * kStrideB + wc] = hi;
-                swl[(wr0 + 4 * j) * kStrideB + wc] = bf16_bits(w - bf16_value(hi));
-            }
-        } else {
+        for (int i = 0; i < kCh; ++i) {
+            const int c = c0 + i < Dc ? c0 + i : Dc - 1;
+            __builtin_memcpy(&s.u[i], up + static_cast<size_t>(c) * l, sizeof(s.u[i]));
 #pragma unroll
-            for (int j = 0; j < kUL; ++j)
-                su[(ur0 + kURows * j) * PP + uc] = u_ok(d0, j) ? to_f32(pu[j]) : 0.0f;
-#pragma unroll
-            for (int j = 0; j < kWL; ++j)
-                sw[(wr0 + 4 * j) * kPadD + wc] = w_ok(d0, j) ? pw[j] : 0.0f;
+            for (int j = 0; j < VP; ++j)
+                if (c0 + i >= Dc) s.u[i].v[j] = from_f32<T>(0.0f);
         }
-        __syncthreads();
-        if (d0 + kDC < Dc) load(d0 + kDC);  // in flight during this chunk's products
-        if constexpr (kBf) {
 #pragma unroll
-            for (int j = 0; j < 4 / KS; ++j) {
-                const int kk = 16 * (ks + KS * j) + 4 * kq;
-                const s16x4 bv =
-                    *reinterpret_cast<const s16x4*>(&su16[(16 * cb + col) * kStrideB + kk]);
+        for (int mb = 0; mb < MB; ++mb) {
+            const int m = 16 * mb + col;
+            const float* wr = Wk + static_cast<size_t>(m < M ? m : M - 1) * Dc;
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    const int wo = (16 * mb + col) * kStrideB + kk;
-                    acc[mb] = mfma16x16x16bf16(*reinterpret_cast<const s16x4*>(&swh[wo]), bv,
-                                               acc[mb]);
-                    acc[mb] = mfma16x16x16bf16(*reinterpret_cast<const s16x4*>(&swl[wo]), bv,
-                                               acc[mb]);
-                }
+            for (int i = 0; i < kCh; ++i) {
+                const float w = wr[c0 + i < Dc ? c0 + i : Dc - 1];
+                s.w[mb][i] = c0 + i < Dc ? w : 0.0f;
             }
-        } else {
+        }
+    };
+    f32x4 acc[MB][VP];
 #pragma unroll
-            for (int j = 0; j < 16 / KS; ++j) {
-                const int kk = 4 * (ks + KS * j);
-                const float bval = su[(kk + kq) * PP + 16 * cb + col];
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int j = 0; j < VP; ++j) acc[mb][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto multiply = [&](const Step<T, MB, VP>& s) {
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int i = 0; i < kCh; ++i)
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
-                    acc[mb] = mfma16x16x4(sw[(16 * mb + col) * kPadD + kk + kq], bval, acc[mb]);
+#pragma unroll
+                    for (int j = 0; j < VP; ++j)
+                        acc[mb][j] = mfma16x16x4(s.w[mb][i], s.u[i].v[j], acc[mb][j]);
+        } else {
+            u32x4 bv[VP];
+#pragma unroll
+            for (int j = 0; j < VP; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    bv[j][i] = s.u[2 * i].v[j].bits |
+                               (static_cast<uint32_t>(s.u[2 * i + 1].v[j].bits) << 16);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                u32x4 hi, lo;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float w0 = s.w[mb][2 * i], w1 = s.w[mb][2 * i + 1];
+                    const uint32_t h0 = bf16_bits(w0), h1 = bf16_bits(w1);
+                    hi[i] = h0 | (h1 << 16);
+                    lo[i] = bf16_bits(w0 - bf16_value(h0)) | (bf16_bits(w1 - bf16_value(h1)) << 16);
+                }
+#pragma unroll
+                for (int j = 0; j < VP; ++j) {
+                    acc[mb][j] = mfma16x16x32(hi, bv[j], acc[mb][j]);
+                    acc[mb][j] = mfma16x16x32(lo, bv[j], acc[mb][j]);
+                }
             }
         }
+    };
+    // Whole steps ks, ks + KS, ..: NB - 1 of them in flight during a step's
+    // products. The loop body is one block without branches, its loads held
+    // ahead of the products (the compiler sinks them to their uses otherwise,
+    // and waits for all loads where paths join); past the last step the last
+    // one is loaded again.
+    const int whole = Dc / kStep;
+    const int mine = ks < whole ? (whole - ks + KS - 1) / KS : 0;
+    if (mine > 0) {
+        Step<T, MB, VP> s[NB];
+        auto at = [&](int i) { return ks + KS * (i < mine ? i : mine - 1); };
+#pragma unroll
+        for (int i = 0; i + 1 < NB; ++i) load(s[i], at(i));
+        int it = 0;
+        for (; it + NB <= mine; it += NB) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                load(s[(i + NB - 1) % NB], at(it + i + NB - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(s[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < NB; ++i)
+            if (it + i < mine) multiply(s[i]);
     }
-    if constexpr (KS > 1) {  // sum the channel slices into slice 0
-        __syncthreads();
-        if (ks > 0) {
+    if (Dc % kStep != 0 && whole % KS == ks) {
+        Step<T, MB, VP> s;
+        load_tail(s, whole);
+        multiply(s);
+    }
+    const int rblocks = (R + 15) / 16;
+    if constexpr (KS > 1) {
+        // The sums of the tile's waves: the upper half hands its own to the
+        // lower, then each wave adds the KS / 2 pair sums for the blocks it
+        // goes on with (the timescale rows, and its share of the B and C
+        // rows). Half the LDS of one slot a wave.
+        constexpr int kHalf = KS / 2;
+        auto slot = [&](int w, int mb, int j) {
+            return reinterpret_cast<f32x4*>(part + (pw * kHalf + w) * kRegs * 256 +
+                                            ((mb * VP + j) * 64 + lane) * 4);
+        };
+        if (ks >= kHalf) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    pool[(((ks - 1) * CB + cb) * MB + mb) * 256 + v * 64 + lane] = acc[mb][v];
+                for (int j = 0; j < VP; ++j) *slot(ks - kHalf, mb, j) = acc[mb][j];
         }
         __syncthreads();
-        if (ks == 0) {
+        if (ks < kHalf) {
 #pragma unroll
-            for (int s = 1; s < KS; ++s)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        acc[mb][v] += pool[(((s - 1) * CB + cb) * MB + mb) * 256 + v * 64 + lane];
+                for (int j = 0; j < VP; ++j) *slot(ks, mb, j) += acc[mb][j];
         }
-    }
-    // B and C rows from the accumulators; the timescale rows to LDS
-    if (ks == 0) {
-        bool ok;
-        const size_t nb = pos_base(16 * cb + col, N, ok);
+        __syncthreads();
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
+            if (mb >= rblocks && mb % KS != ks) continue;
+#pragma unroll
+            for (int j = 0; j < VP; ++j) {
+                f32x4 s = *slot(0, mb, j);
+#pragma unroll
+                for (int w = 1; w < kHalf; ++w) s += *slot(w, mb, j);
+                acc[mb][j] = s;
+            }
+        }
+        if (tile >= tiles) return;
+    }
+
+    // B and C rows
+    if (ok) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            if (KS > 1 && mb % KS != ks) continue;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * mb + 4 * kq + v;
-                const float x = acc[mb][v];
-                if (m < R) {
-                    ss[m * PP + 16 * cb + col] = x;
-                } else if (ok && m < M) {
-                    T* dst = m < R + N ? Bo + nb + static_cast<size_t>(m - R) * l
-                                       : Co + nb + static_cast<size_t>(m - R - N) * l;
-                    *dst = from_f32<T>(x);
-                }
+                if (m < R || m >= M) continue;
+                Vec<T, VP> o;
+#pragma unroll
+                for (int j = 0; j < VP; ++j) o.v[j] = from_f32<T>(acc[mb][j][v]);
+                const int n = m - R;
+                T* dst = n < N ? Bo + (bk * N + n) * l : Co + (bk * N + n - N) * l;
+                __builtin_memcpy(dst + t0, &o, sizeof(o));
             }
         }
     }
-    __syncthreads();  // timescale rows written; the staging pool is free
 
     // 2. delta
+    T* dp = delta + (bk * Dc) * l + t0;
     if (Wdt == nullptr) {
-        // R = 1, Broadcast_D: every channel takes the timescale row; a
-        // thread keeps one position and walks the channels
-        if (!uok) return;
-        const T x = from_f32<T>(ss[uc]);
-        for (int d = ur0; d < Dc; d += kURows) delta[ubase + static_cast<size_t>(d) * l] = x;
+        // R = 1, Broadcast_D: every channel takes x_dbl row 0 (register 0 of
+        // lane group 0); the lane groups share the channels
+        Vec<T, VP> o;
+#pragma unroll
+        for (int j = 0; j < VP; ++j) o.v[j] = from_f32<T>(__shfl(acc[0][j][0], col, 64));
+        if (!ok) return;
+        for (int d = 4 * ks + kq; d < Dc; d += 4 * KS)
+            __builtin_memcpy(dp + static_cast<size_t>(d) * l, &o, sizeof(o));
         return;
     }
-    size_t dbase[CB];
-    bool dok[CB];
+    constexpr int RB = MB < kMaxR / 16 ? MB : kMaxR / 16;  // blocks that may hold timescale rows
+    f32x4 x[RB][VP];
 #pragma unroll
-    for (int c = 0; c < CB; ++c) dbase[c] = pos_base(16 * c + col, Dc, dok[c]);
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int j = 0; j < VP; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[rb][j][v] = 16 * rb + 4 * kq + v < R ? acc[rb][j][v] : 0.0f;
     const float* Wd = Wdt + static_cast<size_t>(k) * Dc * R;
-    constexpr int RS = kMaxR / 4;
-    float* swd = pool;
-    // With a wide x_dbl block (MB >= 4: rank 17 or more at N = 16) the next
-    // chunk of W_dt is loaded into registers while the current one is in
-    // use: at rank 48 (7x7 stage, 1536 channels) each chunk is 12 KB and the
-    // product over it is short, so a load that waits before every chunk left
-    // the matrix cores idle most of the time. At low ranks the chunk is a
-    // few hundred bytes and the extra registers cost more than they hide.
-    constexpr bool kPrefetch = MB >= 4;
-    constexpr int kPf = kPrefetch ? (kDC * kMaxR) / 256 : 1;
-    float pf[kPf];
-    auto fetch = [&](int d0) {
-        const int n = (Dc - d0 < kDC ? Dc - d0 : kDC) * R;
+    // Blocks of 16 channels, the next block's weights in flight during the
+    // current one's products. kVec: R % 4 == 0, a lane's four weights are one
+    // aligned vector, all in or all past the rank (past it, any in-range
+    // value: masked before use). kRB: the blocks of timescale rows there are.
+    auto channels = [&](auto vec_tag, auto rb_tag) __attribute__((always_inline)) {
+        constexpr bool kVec = decltype(vec_tag)::value;
+        constexpr int kRB = decltype(rb_tag)::value < RB ? decltype(rb_tag)::value : RB;
+        auto load_dt = [&](f32x4 (&a)[kRB], int d0) {
+            const int d = d0 + col < Dc ? d0 + col : Dc - 1;
+            const float* row = Wd + static_cast<size_t>(d) * R;
 #pragma unroll
-        for (int j = 0; j < kPf; ++j) {
-            const int i = tid + 256 * j;
-            pf[j] = i < n ? Wd[static_cast<size_t>(d0) * R + i] : 0.0f;
-        }
-    };
-    if constexpr (kPrefetch) fetch(0);
-    for (int d0 = 0; d0 < Dc; d0 += kDC) {
-        // W_dt rows d0 .. d0 + 64 are one contiguous block
-        const int rows = Dc - d0 < kDC ? Dc - d0 : kDC;
-        if constexpr (kPrefetch) {
+            for (int rb = 0; rb < kRB; ++rb) {
+                const int r = 16 * rb + 4 * kq;
+                if constexpr (kVec) {
+                    __builtin_memcpy(&a[rb], row + (r < R ? r : 0), 16);
+                } else {
 #pragma unroll
-            for (int j = 0; j < kPf; ++j) {
-                const int i = tid + 256 * j;
-                if (i < rows * R) {
-                    const int r = i / R, c = i - r * R;
-                    swd[r * kPadR + c] = pf[j];
+                    for (int v = 0; v < 4; ++v) a[rb][v] = row[r + v < R ? r + v : 0];
                 }
             }
-        } else {
-            for (int i = tid; i < rows * R; i += 256) {
-                const int r = i / R, c = i - r * R;
-                swd[r * kPadR + c] = Wd[static_cast<size_t>(d0) * R + i];
-            }
-        }
-        __syncthreads();
-        if constexpr (kPrefetch) {
-            if (d0 + kDC < Dc) fetch(d0 + kDC);  // in flight during this chunk's products
-        }
-        const int dl = 16 * wv + col;  // A-operand row (channel within the chunk)
-        float a[RS];
+        };
+        auto block = [&](const f32x4 (&a)[kRB], int d0) {
+            f32x4 o[VP];
 #pragma unroll
-        for (int rs = 0; rs < RS; ++rs) {
-            const int r = 4 * rs + kq;
-            a[rs] = (r < R && dl < rows) ? swd[dl * kPadR + r] : 0.0f;
-        }
+            for (int j = 0; j < VP; ++j) o[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            f32x4 o = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int rs = 0; rs < RS; ++rs) {
-                const int r = 4 * rs + kq;
-                if (4 * rs < R) o = mfma16x16x4(a[rs], r < R ? ss[r * PP + 16 * c + col] : 0.0f, o);
-            }
-            if (dok[c]) {
+            for (int rb = 0; rb < kRB; ++rb) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int d = d0 + 16 * wv + 4 * kq + v;
-                    if (d < Dc) delta[dbase[c] + static_cast<size_t>(d) * l] = from_f32<T>(o[v]);
+                    const float w = 16 * rb + 4 * kq + v < R ? a[rb][v] : 0.0f;
+#pragma unroll
+                    for (int j = 0; j < VP; ++j) o[j] = mfma16x16x4(w, x[rb][j][v], o[j]);
                 }
             }
+            if (!ok) return;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int d = d0 + 4 * kq + v;
+                Vec<T, VP> s;
+#pragma unroll
+                for (int j = 0; j < VP; ++j) s.v[j] = from_f32<T>(o[j][v]);
+                if (d < Dc) __builtin_memcpy(dp + static_cast<size_t>(d) * l, &s, sizeof(s));
+            }
+        };
+        const int blocks = (Dc + 15) / 16;
+        const int mine = ks < blocks ? (blocks - ks + KS - 1) / KS : 0;
+        if (mine == 0) return;
+        f32x4 a0[kRB], a1[kRB];
+        auto at = [&](int i) { return 16 * (ks + KS * (i < mine ? i : mine - 1)); };
+        load_dt(a0, at(0));
+        int i = 0;
+        for (; i + 2 <= mine; i += 2) {
+            load_dt(a1, at(i + 1));
+            __builtin_amdgcn_sched_barrier(0);
+            block(a0, at(i));
+            load_dt(a0, at(i + 2));
+            __builtin_amdgcn_sched_barrier(0);
+            block(a1, at(i + 1));
         }
-        __syncthreads();  // the W_dt chunk has been read
+        if (i < mine) block(a0, at(i));
+    };
+    auto blocks_of = [&](auto vec_tag) __attribute__((always_inline)) {
+        if (rblocks == 1)
+            channels(vec_tag, std::integral_constant<int, 1>{});
+        else if (rblocks == 2)
+            channels(vec_tag, std::integral_constant<int, 2>{});
+        else
+            channels(vec_tag, std::integral_constant<int, RB>{});
+    };
+    if ((R & 3) == 0)
+        blocks_of(std::true_type{});
+    else
+        blocks_of(std::false_type{});
+}
+
+struct Args {
+    const void* u;
+    const float *W, *W_dt;
+    void *delta, *B, *C;
+    int64_t batch;
+    int K, Dc, L, N, R;
+    hipStream_t s;
+};
+
+template <typename T, int MB, int VP, int KS>
+void launch_mb(const Args& a) {
+    const int64_t groups = a.batch * ((a.L + VP - 1) / VP);
+    const int64_t tiles = (groups + 15) / 16;
+    constexpr int PW = kWaves / KS;
+    const int64_t wgs = (tiles + PW - 1) / PW * a.K;
+    hipLaunchKernelGGL((k_projections<T, MB, VP, KS>), dim3(static_cast<unsigned>(wgs)),
+                       dim3(kThreads), 0, a.s, static_cast<const T*>(a.u), a.W, a.W_dt,
+                       static_cast<T*>(a.delta), static_cast<T*>(a.B), static_cast<T*>(a.C), a.K,
+                       a.Dc, a.L, a.N, a.R, groups, static_cast<int>(tiles));
+}
+
+template <typename T, int VP, int KS>
+void launch_vp(const Args& a) {
+    switch ((a.R + 2 * a.N + 15) / 16) {
+        case 1: return launch_mb<T, 1, VP, KS>(a);
+        case 2: return launch_mb<T, 2, VP, KS>(a);
+        case 3: return launch_mb<T, 3, VP, KS>(a);
+        case 4: return launch_mb<T, 4, VP, KS>(a);
+        case 5: return launch_mb<T, 5, VP, KS>(a);
+        default: return launch_mb<T, 6, VP, KS>(a);
     }
 }
 
-// widest tile whose grid still gives every compute unit two workgroups
-int column_blocks(int64_t positions, int64_t K) {
-    for (int cb : {4, 2}) {
-        const int64_t tiles = (positions + 16 * cb - 1) / (16 * cb);
-        if (tiles * K >= 2 * 256) return cb;
-    }
-    return 1;
-}
-
-template <typename T, int MB, int CB>
-void launch_mb(int64_t positions, hipStream_t s, const void* u, const float* W, const float* W_dt,
-               void* delta, void* B, void* C, int K, int Dc, int L, int N, int R) {
-    const int64_t tiles = (positions + 16 * CB - 1) / (16 * CB);
-    hipLaunchKernelGGL((k_projections<T, MB, CB>), dim3(static_cast<unsigned>(tiles * K)),
-                       dim3(256), 0, s, static_cast<const T*>(u), W, W_dt, static_cast<T*>(delta),
-                       static_cast<T*>(B), static_cast<T*>(C), K, Dc, L, N, R, positions,
-                       static_cast<int>(tiles));
-}
-
-template <typename T, int CB>
-void launch_cb(int mb, int64_t positions, hipStream_t s, const void* u, const float* W,
-               const float* W_dt, void* delta, void* B, void* C, int K, int Dc, int L, int N,
-               int R) {
-    switch (mb) {
-        case 1: return launch_mb<T, 1, CB>(positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-        case 2: return launch_mb<T, 2, CB>(positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-        case 3: return launch_mb<T, 3, CB>(positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-        case 4: return launch_mb<T, 4, CB>(positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-        case 5: return launch_mb<T, 5, CB>(positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-        default: return launch_mb<T, 6, CB>(positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-    }
-}
-
+// Tile width and channel split. Measured (us; four waves a tile, two, one, or
+// two positions a lane and four waves), VMamba stages at batch 32:
+//   28x28 fp32 rank 12      1568 tiles   100  112  107  111
+//   14x14 bf16 rank 24       392 tiles    39   42   68   48
+//   7x7 fp32 rank 48         104 tiles    66  122  232   45
+//   128 x 56x56 bf16 rank 6  25088 tiles  372  314  312  524
+//   2 x 128x512 fp32 rank 6  8192 tiles   217  210  215  252
+// so four waves share a tile until the tiles alone fill the chip several
+// times over (then two: less to exchange), and tiles get narrower only when
+// there are fewer than compute units. Sequences shorter than a vector take
+// single positions.
 template <typename T>
-void launch_t(int mb, int64_t positions, hipStream_t s, const void* u, const float* W,
-              const float* W_dt, void* delta, void* B, void* C, int K, int Dc, int L, int N,
-              int R) {
-    const int cb = column_blocks(positions, K);
-    if (cb == 4) return launch_cb<T, 4>(mb, positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-    if (cb == 2) return launch_cb<T, 2>(mb, positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
-    return launch_cb<T, 1>(mb, positions, s, u, W, W_dt, delta, B, C, K, Dc, L, N, R);
+void launch_t(const Args& a) {
+    const int64_t tiles4 = (a.batch * ((a.L + 3) / 4) + 15) / 16 * a.K;
+    if (a.L < 4) return launch_vp<T, 1, 4>(a);
+    if (tiles4 < 256) return launch_vp<T, 2, 4>(a);
+    if (tiles4 >= 4096) return launch_vp<T, 4, 2>(a);
+    launch_vp<T, 4, 4>(a);
 }
 
 }  // namespace
@@ -389,16 +460,13 @@ void launch_t(int mb, int64_t positions, hipStream_t s, const void* u, const flo
 vmb_status launch_projections(const void* u, const float* W, const float* W_dt, void* delta,
                               void* B, void* C, int64_t batch, int64_t K, int64_t channels,
                               int64_t L, int64_t N, int64_t R, vmb_dtype dt, hipStream_t s) {
-    const int64_t positions = batch * L;
-    if (R > kMaxR || R + 2 * N > 16 * kMaxMB || (positions + 15) / 16 * K > int64_t{0x7fffffff})
+    if (R > kMaxR || R + 2 * N > 16 * kMaxMB || (batch * L + 15) / 16 * K > int64_t{0x7fffffff})
         return VMB_ERR_UNSUPPORTED;
-    const int mb = static_cast<int>((R + 2 * N + 15) / 16);
+    const Args a{u, W, W_dt, delta, B, C, batch, int(K), int(channels), int(L), int(N), int(R), s};
     if (dt == VMB_F32)
-        launch_t<float>(mb, positions, s, u, W, W_dt, delta, B, C, int(K), int(channels), int(L),
-                        int(N), int(R));
+        launch_t<float>(a);
     else
-        launch_t<bf16_t>(mb, positions, s, u, W, W_dt, delta, B, C, int(K), int(channels), int(L),
-                         int(N), int(R));
+        launch_t<bf16_t>(a);
     return check_launch();
 }
 
