@@ -149,11 +149,12 @@ __device__ __forceinline__ void pin(float (&v)[T]) {
 }
 
 // smallest number of waves per SIMD the registers are budgeted for: what the
-// fused form's LDS admits at 56x56 (12 or 16 bytes a pixel), and the same
-// budget elsewhere (two fp32 states at a time need about 150 registers)
-template <typename Tin, int NP>
+// fused form's LDS admits at 56x56 (12 or 16 bytes a pixel and channel), and
+// the same budget elsewhere (two fp32 chains at a time need about 150
+// registers)
+template <typename Tin, int kChains, int kMode>
 constexpr int row_waves() {
-    return sizeof(Tin) == 4 && NP == 2 ? 3 : 4;
+    return kChains == 2 && (sizeof(Tin) == 4 || kMode == kMapRows) ? 3 : 4;
 }
 
 struct RowArgs {
@@ -172,10 +173,12 @@ struct RowArgs {
     unsigned n_wg;  // whole grid, 0 when it is not renumbered
 };
 
-template <int S, int T, int NP, typename Tin, typename Tout, int kMode, bool kZoh>
-__global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_scan_rows(
+template <int S, int T, int CH, int NP, typename Tin, typename Tout, int kMode, bool kZoh, bool kN1>
+__global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) void k_full_scan_rows(
     const RowArgs g) {
-    constexpr int kCpw = kWave / S;  // sequences (channels) per wave
+    constexpr int kCpw = kWave / S;   // sequences (channels) side by side in a wave
+    constexpr int kPlanes = CH * kCpw;  // channels of a wave
+    constexpr int kX = CH * NP;       // recurrences a lane runs at a time: x = h NP + s
     constexpr int kChunk = S * T;
     extern __shared__ __align__(16) char lds[];
 
@@ -183,7 +186,7 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
     const int lane = tid % kWave;
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int cw = lane / S, sl = lane % S;
-    const int Dc = g.Dc, N = NP == 1 ? 1 : g.N;  // N is 1 or even
+    const int Dc = g.Dc, N = kN1 ? 1 : g.N;  // a multiple of NP
     const int64_t L = g.L;
 
     // Workgroup i runs on XCD i % 8 (own L2): each XCD takes a contiguous
@@ -203,42 +206,54 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
         b = blockIdx.z;
     }
     if constexpr (kMode == kFused) k = wv;  // gridDim.y is 1
-    const int d0 = kMode == kFused ? grp * kCpw : (grp * kRowWaves + wv) * kCpw;
+    const int d0 = kMode == kFused ? grp * kPlanes : (grp * kRowWaves + wv) * kPlanes;
     if (kMode != kFused && d0 >= Dc) return;
-    const int nc = Dc - d0 < kCpw ? Dc - d0 : kCpw;   // channels of this wave
-    const int cc = cw < nc ? cw : nc - 1;             // slots past them repeat the last, unstored
+    const int nc = Dc - d0 < kPlanes ? Dc - d0 : kPlanes;  // channels of this wave
+    int slot_of[CH], cc[CH];  // this lane's channels; slots past nc repeat the last, unstored
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+        slot_of[h] = h * kCpw + cw;
+        cc[h] = slot_of[h] < nc ? slot_of[h] : nc - 1;
+    }
     const int64_t bk = static_cast<int64_t>(b) * g.K + k;
-    const int c = k * Dc + d0 + cc;
     const int iL = kMode == kSeq ? 0 : static_cast<int>(L);  // 2-D maps: L = H * W fits an int
 
     // fused: LDS planes (rows of Lp elements): input in both scan orders,
     // then the outputs of both
     const int Lp = kMode == kFused ? (iL + T - 1) / T * T : 0;
     Tin* u_rows = reinterpret_cast<Tin*>(lds);
-    Tin* u_cols = u_rows + kCpw * Lp;
-    float* y_planes = reinterpret_cast<float*>(u_cols + kCpw * Lp);
+    Tin* u_cols = u_rows + kPlanes * Lp;
+    float* y_planes = reinterpret_cast<float*>(u_cols + kPlanes * Lp);
     const bool rev = kMode == kFused && k >= 2;
     const int lead = rev ? Lp - iL : 0;  // identity positions ahead of the sequence
 
     const int64_t rows = static_cast<int64_t>(g.batch) * g.K;
-    const int64_t row0 = (bk * Dc + d0) * L;  // first channel's delta row
     const Tin* delta = static_cast<const Tin*>(g.delta);
     const Tin* Bm = static_cast<const Tin*>(g.B);
     const Tin* Cm = static_cast<const Tin*>(g.C);
-    const float bias = g.dt_bias ? g.dt_bias[c] : 0.0f;
-    const float dskip = g.D ? g.D[c] : 0.0f;
     const bool sp = g.softplus != 0;
-    const float* Ac = g.A + static_cast<size_t>(c) * N;
+    float bias[CH], dskip[CH];
+    const float* Ac[CH];
+    int64_t row0[CH];  // delta row of the channel (of the first of its segments)
+    int loff[CH];      // this lane's first position from there
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+        const int c = k * Dc + d0 + cc[h];
+        bias[h] = g.dt_bias ? g.dt_bias[c] : 0.0f;
+        dskip[h] = g.D ? g.D[c] : 0.0f;
+        Ac[h] = g.A + static_cast<size_t>(c) * N;
+        // one channel a wave: cc is uniform and the base takes it
+        row0[h] = (bk * Dc + d0 + (kCpw > 1 ? 0 : (h < nc ? h : nc - 1))) * L;
+        loff[h] = (kCpw > 1 ? cc[h] * static_cast<int>(L) : 0) + sl * T - lead;
+    }
 
-    // one chunk's run of delta: base at the chunk, lane offsets in 32 bits
-    const int loff = (kCpw > 1 ? cc * static_cast<int>(L) : 0) + sl * T - lead;
-    auto load_row = [&](const Tin* base, int64_t c0, Run<Tin, T>& r) {
-        const int row_first = kCpw > 1 ? cc * static_cast<int>(L) : -near(c0);
+    // one chunk's run of a row: base at the chunk, lane offsets in 32 bits
+    auto load_row = [&](const Tin* base, int64_t c0, int h, Run<Tin, T>& r) {
+        const int row_first = kCpw > 1 ? cc[h] * static_cast<int>(L) : -near(c0);
         const int row_last = kCpw > 1 ? row_first + static_cast<int>(L) - 1 : near(L - 1 - c0);
-        load_run<Tin, T>(base + row0 + c0, loff, -near(row0 + c0),
-                         near(rows * Dc * L - row0 - c0), row_first, row_last, r);
+        load_run<Tin, T>(base + row0[h] + c0, loff[h], -near(row0[h] + c0),
+                         near(rows * Dc * L - row0[h] - c0), row_first, row_last, r);
     };
-    auto load_delta = [&](int64_t c0, Run<Tin, T>& r) { load_row(delta, c0, r); };
     auto load_state = [&](const Tin* base, int64_t c0, int n, Run<Tin, T>& r) {
         const int64_t at = (bk * N + n) * L + c0;
         load_run<Tin, T>(base + at, sl * T - lead, -near(at), near(rows * N * L - at), -near(c0),
@@ -246,14 +261,14 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
     };
     // u of a chunk from global memory: the sequence's own row, or (kMapRows)
     // the plane read in direction k's order
-    auto load_u = [&](int64_t c0, Run<Tin, T>& r, bool& reversed) {
+    auto load_u = [&](int64_t c0, int h, Run<Tin, T>& r, bool& reversed) {
         reversed = false;
         const Tin* u = static_cast<const Tin*>(g.u);
         if constexpr (kMode == kSeq) {
-            load_row(u, c0, r);
+            load_row(u, c0, h, r);
         } else {
             const Tin* src = (k & 1) && g.xt ? static_cast<const Tin*>(g.xt) : u;
-            const int64_t p0 = (static_cast<int64_t>(b) * Dc + d0) * L;
+            const int64_t p0 = (static_cast<int64_t>(b) * Dc + d0 + (h < nc ? h : nc - 1)) * L;
             const int64_t t0 = c0 + sl * T;
             if (!(k & 1) || g.xt) {
                 reversed = k >= 2;
@@ -267,15 +282,15 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
                 Tin e[T];
                 const int ts = t0 < L ? static_cast<int>(t0) : iL - 1;
                 const int tt = k >= 2 ? iL - 1 - ts : ts;
-                int w = tt / g.H, h = tt - w * g.H;
+                int pw = tt / g.H, ph = tt - pw * g.H;
 #pragma unroll
                 for (int i = 0; i < T; ++i) {
-                    e[i] = src[p0 + static_cast<int64_t>(h) * g.W + w];
+                    e[i] = src[p0 + static_cast<int64_t>(ph) * g.W + pw];
                     if (t0 + i + 1 < L) {
                         if (k < 2) {
-                            if (++h == g.H) { h = 0; ++w; }
+                            if (++ph == g.H) { ph = 0; ++pw; }
                         } else {
-                            if (--h < 0) { h = g.H - 1; --w; }
+                            if (--ph < 0) { ph = g.H - 1; --pw; }
                         }
                     }
                 }
@@ -284,20 +299,26 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
         }
     };
 
-    Run<Tin, T> draw;
-    load_delta(0, draw);
-    Run<Tin, T> uraw;
+    Run<Tin, T> draw[CH], uraw[CH];
     bool urev = false;
-    if constexpr (kMode != kFused) load_u(0, uraw, urev);
+    auto load_chunk = [&](int64_t c0) {
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            load_row(delta, c0, h, draw[h]);
+            if constexpr (kMode != kFused) load_u(c0, h, uraw[h], urev);
+        }
+    };
+    load_chunk(0);
 
     Run<Tin, T> braw[NP], craw[NP];
-    float araw[NP];
+    float araw[kX];
     auto load_states = [&](int64_t c0, int n) {
 #pragma unroll
         for (int s = 0; s < NP; ++s) {
             load_state(Bm, c0, n + s, braw[s]);
             load_state(Cm, c0, n + s, craw[s]);
-            araw[s] = Ac[n + s];
+#pragma unroll
+            for (int h = 0; h < CH; ++h) araw[h * NP + s] = Ac[h][n + s];
         }
     };
     load_states(0, 0);
@@ -305,8 +326,7 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
     if constexpr (kMode == kFused) {
         // the channels' planes into both scan orders, vectors of kPer pixels
         constexpr int kPer = 16 / static_cast<int>(sizeof(Tin));
-        constexpr int kThr = kRowThreads / kCpw;  // threads per plane
-        static_assert(kCpw == 1 || kThr * 4 >= S * T, "one pass over short planes");
+        constexpr int kThr = kRowThreads / kPlanes;  // threads per plane
         const int ch = tid / kThr;
         const Tin* x = static_cast<const Tin*>(g.u) +
                        (static_cast<size_t>(b) * Dc + d0 + (ch < nc ? ch : 0)) * iL;
@@ -336,128 +356,136 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
         }
         __syncthreads();
     }
-    const Tin* u_plane = ((k & 1) ? u_cols : u_rows) + cc * Lp;
-    float* y_plane = y_planes + ((k & 1) * kCpw + cw) * Lp;
     // the middle chunk, around which the two directions of a plane exchange
     // (kFused, step 4)
     const int chunks = kMode == kFused ? (Lp + kChunk - 1) / kChunk : 0;
     const int64_t middle = kMode == kFused ? static_cast<int64_t>((chunks - 1) / 2) * kChunk : -1;
 
-    float carry = 0.0f;  // lane n: state n leaving the previous chunk
+    float carry[CH];  // lane n: state n leaving the previous chunk
+#pragma unroll
+    for (int h = 0; h < CH; ++h) carry[h] = 0.0f;
     for (int64_t c0 = 0; c0 < L + lead; c0 += kChunk) {
-        // 1. per-position products of the run
-        float uv[T];
+        // 1. per-position products of the runs
         int at = 0;  // fused: the run's first element in its plane
         bool in_plane = true;
         if constexpr (kMode == kFused) {
             const int t0 = static_cast<int>(c0) + sl * T;
             at = rev ? Lp - T - t0 : t0;
             in_plane = at >= 0 && at < Lp;
-            Run<Tin, T> r;
-            __builtin_memcpy(&r, __builtin_assume_aligned(u_plane + (in_plane ? at : 0),
-                                                          sizeof(Tin) * T < 16 ? 8 : 16),
-                             sizeof(r));
-#pragma unroll
-            for (int i = 0; i < T; ++i) uv[i] = rev ? run_at(r, T - 1 - i) : run_at(r, i);
-        } else {
-#pragma unroll
-            for (int i = 0; i < T; ++i) uv[i] = urev ? run_at(uraw, T - 1 - i) : run_at(uraw, i);
-        }
-        float dl2[T], du[T], yv[T];
-        float s2 = 0.0f;
-#pragma unroll
-        for (int i = 0; i < T; ++i) dl2[i] = run_at(draw, i) + bias;
-        if (sp) {
-#pragma unroll
-            for (int i = 0; i < T; ++i) dl2[i] = softplus(dl2[i]);
         }
         const bool led = kMode == kFused && lead > 0 && c0 == 0;
-        if (led) {  // identity positions ahead of a reversed sequence
+        float uv[CH][T], dl2[CH][T], du[CH][T], yv[CH][T], s2[CH];
 #pragma unroll
-            for (int i = 0; i < T; ++i) {
-                if (sl == 0 && i < lead) dl2[i] = uv[i] = 0.0f;
-                asm volatile("" : "+v"(dl2[i]), "+v"(uv[i]));  // a branch of its own
+        for (int h = 0; h < CH; ++h) {
+            if constexpr (kMode == kFused) {
+                const Tin* src = ((k & 1) ? u_cols : u_rows) + cc[h] * Lp + (in_plane ? at : 0);
+                Run<Tin, T> r;
+                __builtin_memcpy(&r, __builtin_assume_aligned(src, sizeof(Tin) * T < 16 ? 8 : 16),
+                                 sizeof(r));
+#pragma unroll
+                for (int i = 0; i < T; ++i) uv[h][i] = rev ? run_at(r, T - 1 - i) : run_at(r, i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+                    uv[h][i] = urev ? run_at(uraw[h], T - 1 - i) : run_at(uraw[h], i);
             }
-        }
 #pragma unroll
-        for (int i = 0; i < T; ++i) {
-            du[i] = dl2[i] * uv[i];
-            dl2[i] *= kLog2e;
-            yv[i] = dskip * uv[i];
-            s2 += dl2[i];
-        }
-        // the loads below reuse the raw registers
-        pin(dl2), pin(du), pin(yv);
-        // 2. the next chunk's delta (and u) in flight during the states
-        const bool more = c0 + kChunk < L + lead;
-        if (more) {
-            load_delta(c0 + kChunk, draw);
-            if constexpr (kMode != kFused) load_u(c0 + kChunk, uraw, urev);
-        }
-        // 3. the states, NP at a time
-#pragma unroll 1
-        for (int n = 0; n < N; n += NP) {
-            float an[NP], a[NP][T], bu[NP][T], cv[NP][T], P[NP], Hs[NP];
+            for (int i = 0; i < T; ++i) dl2[h][i] = run_at(draw[h], i) + bias[h];
+            if (sp) {
 #pragma unroll
-            for (int s = 0; s < NP; ++s) {
-                an[s] = araw[s];
+                for (int i = 0; i < T; ++i) dl2[h][i] = softplus(dl2[h][i]);
+            }
+            if (led) {  // identity positions ahead of a reversed sequence
 #pragma unroll
                 for (int i = 0; i < T; ++i) {
-                    bu[s][i] = run_at(braw[s], i);
+                    if (sl == 0 && i < lead) dl2[h][i] = uv[h][i] = 0.0f;
+                    asm volatile("" : "+v"(dl2[h][i]), "+v"(uv[h][i]));  // a branch of its own
+                }
+            }
+            s2[h] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                du[h][i] = dl2[h][i] * uv[h][i];
+                dl2[h][i] *= kLog2e;
+                yv[h][i] = dskip[h] * uv[h][i];
+                s2[h] += dl2[h][i];
+            }
+            // the loads below reuse the raw registers
+            pin(dl2[h]), pin(du[h]), pin(yv[h]);
+        }
+        // 2. the next chunk's delta (and u) in flight during the states
+        const bool more = c0 + kChunk < L + lead;
+        if (more) load_chunk(c0 + kChunk);
+        // 3. the states, NP at a time, for each of the lane's channels: the
+        //    recurrences' chains are independent of each other
+#pragma unroll 1
+        for (int n = 0; n < N; n += NP) {
+            float an[kX], a[kX][T], bu[kX][T], bv[NP][T], cv[NP][T], P[kX], Hs[kX];
+#pragma unroll
+            for (int s = 0; s < NP; ++s) {
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    bv[s][i] = run_at(braw[s], i);
                     cv[s][i] = run_at(craw[s], i);
                 }
                 // the loads below reuse the raw registers
-                pin(bu[s]), pin(cv[s]);
-                asm volatile("" : "+v"(an[s]));
+                pin(bv[s]), pin(cv[s]);
                 if (led) {
 #pragma unroll
                     for (int i = 0; i < T; ++i) {
-                        if (sl == 0 && i < lead) bu[s][i] = 0.0f;
-                        asm volatile("" : "+v"(bu[s][i]));
+                        if (sl == 0 && i < lead) bv[s][i] = 0.0f;
+                        asm volatile("" : "+v"(bv[s][i]));
                     }
                 }
+            }
+#pragma unroll
+            for (int x = 0; x < kX; ++x) {
+                an[x] = araw[x];
+                asm volatile("" : "+v"(an[x]));
             }
             if (n + NP < N)
                 load_states(c0, n + NP);
             else if (more)
                 load_states(c0 + kChunk, 0);
 #pragma unroll
-            for (int s = 0; s < NP; ++s) {
-                const float inv_a = kZoh ? 1.0f / an[s] : 0.0f;
+            for (int x = 0; x < kX; ++x) {
+                const int h = x / NP, s = x % NP;
+                const float inv_a = kZoh ? 1.0f / an[x] : 0.0f;
                 float agg = 0.0f;
 #pragma unroll
                 for (int i = 0; i < T; ++i) {
-                    const float x2 = dl2[i] * an[s];
-                    a[s][i] = fast_exp2(x2);
-                    const float q = kZoh ? zoh_q(x2, a[s][i], du[i], uv[i], inv_a) : du[i];
-                    bu[s][i] *= q;
-                    agg = i == 0 ? bu[s][0] : __builtin_fmaf(a[s][i], agg, bu[s][i]);
+                    const float x2 = dl2[h][i] * an[x];
+                    a[x][i] = fast_exp2(x2);
+                    const float q = kZoh ? zoh_q(x2, a[x][i], du[h][i], uv[h][i], inv_a) : du[h][i];
+                    bu[x][i] = q * bv[s][i];
+                    agg = i == 0 ? bu[x][0] : __builtin_fmaf(a[x][i], agg, bu[x][i]);
                 }
-                P[s] = fast_exp2(s2 * an[s]);
-                Hs[s] = agg;
+                P[x] = fast_exp2(s2[h] * an[x]);
+                Hs[x] = agg;
             }
-            if constexpr (NP == 2 && S == kWave) {
+            if constexpr (kX == 2 && S == kWave) {
                 wave_scan2(P[0], Hs[0], P[1], Hs[1]);
             } else {
 #pragma unroll
-                for (int s = 0; s < NP; ++s) scan_lanes<S>(P[s], Hs[s]);
+                for (int x = 0; x < kX; ++x) scan_lanes<S>(P[x], Hs[x]);
             }
 #pragma unroll
-            for (int s = 0; s < NP; ++s) {
-                float h;
+            for (int x = 0; x < kX; ++x) {
+                const int h = x / NP, s = x % NP;
+                float hs;
                 if constexpr (S == kWave) {
-                    const float cin = lane_value(carry, n + s);
-                    const float out = __builtin_fmaf(P[s], cin, Hs[s]);
-                    h = shr1(cin, out);  // lane 0 keeps the chunk's carry
-                    carry = lane == n + s ? lane_value(out, kWave - 1) : carry;
+                    const float cin = lane_value(carry[h], n + s);
+                    const float out = __builtin_fmaf(P[x], cin, Hs[x]);
+                    hs = shr1(cin, out);  // lane 0 keeps the chunk's carry
+                    carry[h] = lane == n + s ? lane_value(out, kWave - 1) : carry[h];
                 } else {
-                    const float in = shr1(0.0f, Hs[s]);
-                    h = sl == 0 ? 0.0f : in;
+                    const float in = shr1(0.0f, Hs[x]);
+                    hs = sl == 0 ? 0.0f : in;
                 }
 #pragma unroll
                 for (int i = 0; i < T; ++i) {
-                    h = __builtin_fmaf(a[s][i], h, bu[s][i]);
-                    yv[i] = __builtin_fmaf(cv[s][i], h, yv[i]);
+                    hs = __builtin_fmaf(a[x][i], hs, bu[x][i]);
+                    yv[h][i] = __builtin_fmaf(cv[s][i], hs, yv[h][i]);
                 }
             }
         }
@@ -473,23 +501,33 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
             const int other = (rev ? at : Lp - T - at) / kChunk;
             const int mine = static_cast<int>(c0 / kChunk);
             const bool add = in_plane && (rev ? other <= mine : other < mine);
-            if (c0 == middle) __syncthreads();
-            if (!rev && in_plane) put_run<T>(y_plane + at, yv, false, add);
-            if (c0 == middle) __syncthreads();
-            if (rev && in_plane) put_run<T>(y_plane + at, yv, true, add);
-            if (c0 == middle) __syncthreads();
-        } else if (cw < nc) {
-            const int left = near(L - c0);
-            Tout* yrow = static_cast<Tout*>(g.y) + row0 + c0 + loff;
-            Tout o[T];
+            float* dst = y_planes + ((k & 1) * kPlanes + cw) * Lp + at;
+            auto put = [&]() {
+                if (in_plane)
 #pragma unroll
-            for (int i = 0; i < T; ++i) o[i] = from_f32<Tout>(yv[i]);
-            if (sl * T + T <= left) {
-                __builtin_memcpy(yrow, o, sizeof(o));
-            } else {
+                    for (int h = 0; h < CH; ++h) put_run<T>(dst + h * kCpw * Lp, yv[h], rev, add);
+            };
+            if (c0 == middle) __syncthreads();
+            if (!rev) put();
+            if (c0 == middle) __syncthreads();
+            if (rev) put();
+            if (c0 == middle) __syncthreads();
+        } else {
 #pragma unroll
-                for (int i = 0; i < T; ++i)
-                    if (sl * T + i < left) yrow[i] = o[i];
+            for (int h = 0; h < CH; ++h) {
+                if (slot_of[h] >= nc) continue;
+                const int left = near(L - c0);
+                Tout* yrow = static_cast<Tout*>(g.y) + row0[h] + c0 + loff[h];
+                Tout o[T];
+#pragma unroll
+                for (int i = 0; i < T; ++i) o[i] = from_f32<Tout>(yv[h][i]);
+                if (sl * T + T <= left) {
+                    __builtin_memcpy(yrow, o, sizeof(o));
+                } else {
+#pragma unroll
+                    for (int i = 0; i < T; ++i)
+                        if (sl * T + i < left) yrow[i] = o[i];
+                }
             }
         }
     }
@@ -497,12 +535,12 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
     if constexpr (kMode == kFused) {
         __syncthreads();
         const int H = g.H, W = g.W;
-        constexpr int kThr = kRowThreads / kCpw;  // threads per plane, 4 pixels each
+        constexpr int kThr = kRowThreads / kPlanes;  // threads per plane, 4 pixels each
         const int ch = tid / kThr;
         if (ch >= nc) return;
         Tout* out = static_cast<Tout*>(g.y) + (static_cast<size_t>(b) * Dc + d0 + ch) * iL;
         const float* yr = y_planes + ch * Lp;
-        const float* yc = y_planes + (kCpw + ch) * Lp;
+        const float* yc = y_planes + (kPlanes + ch) * Lp;
         int p = (tid % kThr) * 4;
         int h = p / W, w = p - h * W;
         const int dh = 4 * kThr / W, dw = 4 * kThr - dh * W;
@@ -532,8 +570,12 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, NP>())) void k_full_sc
 
 // ------------------------------------------------------------------ launch
 
-// Largest LDS a fused workgroup takes.
-constexpr size_t kFusedLds = 160 * 1024;
+// LDS of a fused workgroup, at most. Two workgroups a CU or more; a plane that
+// leaves room for only one costs less than the merge pass with one or two
+// states and more with many (97x101, 768 rows of sequences: N = 1 33 against
+// 64 us, with 3072 rows 95 against 167 and N = 8 276 against 220).
+constexpr size_t kCuLds = 160 * 1024;
+inline size_t fused_lds_limit(int64_t N) { return N <= 2 ? kCuLds : kCuLds / 2; }
 
 inline int row_len(int64_t L, int T) { return static_cast<int>((L + T - 1) / T * T); }
 
@@ -541,10 +583,10 @@ size_t fused_lds(int64_t L, int cpw, int T, size_t in_size) {
     return static_cast<size_t>(cpw) * row_len(L, T) * 2 * (in_size + sizeof(float));
 }
 
-template <int S, int T, int NP, typename Tin, typename Tout, int kMode, bool kZoh>
+template <int S, int T, int CH, int NP, typename Tin, typename Tout, int kMode, bool kZoh, bool kN1>
 vmb_status launch_rows(const ScanArgs& a, void* y, const void* xt) {
-    constexpr int kCpw = kWave / S;
-    const int64_t per = kMode == kFused ? kCpw : kCpw * kRowWaves;
+    constexpr int kPlanes = CH * (kWave / S);
+    const int64_t per = kMode == kFused ? kPlanes : kPlanes * kRowWaves;
     const int64_t groups = (a.channels + per - 1) / per;
     if (groups > 0x7fffffffLL) return VMB_ERR_UNSUPPORTED;
     const int64_t gy = kMode == kFused ? 1 : a.K;
@@ -552,22 +594,35 @@ vmb_status launch_rows(const ScanArgs& a, void* y, const void* xt) {
     RowArgs g{a.u, a.delta, a.A, a.B, a.C, a.D, a.dt_bias, y, xt,
               int(a.batch), int(a.K), int(a.channels), int(a.N), int(a.H), int(a.W), a.softplus,
               a.L, int(groups), n_wg <= 0x7fffffffLL ? static_cast<unsigned>(n_wg) : 0u};
-    const size_t lds = kMode == kFused ? fused_lds(a.L, kCpw, T, sizeof(Tin)) : 0;
+    const size_t lds = kMode == kFused ? fused_lds(a.L, kPlanes, T, sizeof(Tin)) : 0;
     const dim3 grid(static_cast<unsigned>(groups), static_cast<unsigned>(gy),
                     static_cast<unsigned>(a.batch));
-    hipLaunchKernelGGL((k_full_scan_rows<S, T, NP, Tin, Tout, kMode, kZoh>), grid,
+    hipLaunchKernelGGL((k_full_scan_rows<S, T, CH, NP, Tin, Tout, kMode, kZoh, kN1>), grid,
                        dim3(kRowThreads), lds, a.stream, g);
     return check_launch();
 }
 
+// Two recurrences at a time per lane: two channels, which share the B and C
+// they read, or two states of one channel (one, with one state). Two channels
+// need half the reads from L2 (32 x 56x56, 192 channels, N = 16, fp32 in
+// sequence layout: 601 -> 504 us; 32 x 28x28, 384 channels, 2-D 390 -> 296),
+// but half the waves: taken when that leaves every SIMD two of them, and in
+// the fused form only while LDS still admits four workgroups a CU (32 x 56x56,
+// bf16, N = 8: 360 against 322 us).
 template <int S, int T, typename Tin, typename Tout, int kMode>
 vmb_status launch_np(const ScanArgs& a, void* y, const void* xt) {
     const bool zoh = (a.options & VMB_SCAN_ZOH) != 0;
-    if (a.N == 1)
-        return zoh ? launch_rows<S, T, 1, Tin, Tout, kMode, true>(a, y, xt)
-                   : launch_rows<S, T, 1, Tin, Tout, kMode, false>(a, y, xt);
-    return zoh ? launch_rows<S, T, 2, Tin, Tout, kMode, true>(a, y, xt)
-               : launch_rows<S, T, 2, Tin, Tout, kMode, false>(a, y, xt);
+    constexpr int kCpw = kWave / S;
+    const bool two = a.batch * a.K * a.channels >= 2 * kCpw * 2048 &&
+                     (kMode != kFused || fused_lds(a.L, 2 * kCpw, T, sizeof(Tin)) <= kCuLds / 4);
+    if (a.N == 1) {
+        if (zoh) return launch_rows<S, T, 1, 1, Tin, Tout, kMode, true, true>(a, y, xt);
+        return two ? launch_rows<S, T, 2, 1, Tin, Tout, kMode, false, true>(a, y, xt)
+                   : launch_rows<S, T, 1, 1, Tin, Tout, kMode, false, true>(a, y, xt);
+    }
+    if (zoh) return launch_rows<S, T, 1, 2, Tin, Tout, kMode, true, false>(a, y, xt);
+    return two ? launch_rows<S, T, 2, 1, Tin, Tout, kMode, false, false>(a, y, xt)
+               : launch_rows<S, T, 1, 2, Tin, Tout, kMode, false, false>(a, y, xt);
 }
 
 // Segment and run length: the shortest pass that holds the sequence (16 lanes
@@ -582,7 +637,7 @@ vmb_status launch_shape(const ScanArgs& a, void* y, const void* xt) {
 
 bool fused_fits(const ScanArgs& a) {
     const size_t in = a.in_dt == VMB_F32 ? 4 : 2;
-    return a.L <= 16384 && fused_lds(a.L, 1, 8, in) <= kFusedLds;
+    return a.L <= 16384 && fused_lds(a.L, 1, 8, in) <= fused_lds_limit(a.N);
 }
 
 template <typename Tin, typename Tout>

@@ -84,6 +84,25 @@ def test_odd_bf16_rows_n16(layout, H, W):
                      what=f"odd 2d {H}x{W}")
 
 
+# enough rows for two channels a lane (4096 whole-wave sequences, 8192 and
+# 16384 of the segments), with a channel left over, and N = 16 in bf16
+@pytest.mark.parametrize("layout,b,H,W,c,N,dtype", [
+    ("seq", 9, 1, 515, 115, 4, "f32"), ("2d", 9, 17, 31, 115, 1, "bf16"),
+    ("2d", 9, 13, 15, 229, 2, "f32"), ("seq", 9, 9, 9, 457, 1, "bf16"),
+    ("2d", 9, 7, 7, 459, 8, "f32"), ("2d", 3, 21, 23, 103, 16, "bf16"),
+    ("seq", 9, 21, 23, 117, 16, "bf16"), ("2d", 2, 95, 101, 151, 16, "bf16")])
+def test_two_channels_a_lane(layout, b, H, W, c, N, dtype):
+    log(f"rows {layout} b={b} {H}x{W} c={c} N={N} {dtype}")
+    inp = inputs(b, H, W, c, N, layout, dtype, d_value=1.0)
+    got = to_f64(run_scan(inp, "full", layout, out_dtype=torch.float32))
+    if layout == "seq":
+        assert_close(got, oracle_seq(inp, "full", "seq"), **FP32_TOL, what=f"{H}x{W} c={c}")
+    else:
+        ref, scale = merged_oracle(inp, "full")
+        assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                     what=f"2d {H}x{W} c={c}")
+
+
 @pytest.mark.parametrize("N", [1, 8])
 @pytest.mark.parametrize("layout,H,W", [("seq", 1, 530), ("2d", 6, 7), ("2d", 23, 25),
                                         ("2d", 90, 91)])
