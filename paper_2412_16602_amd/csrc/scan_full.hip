@@ -10,17 +10,27 @@
 
 namespace vmb {
 
-// The chunked kernel copies B and C rows into LDS in pieces of 4 or 16
-// bytes; a bf16 row of odd length has neither its start nor its end on a
-// 4-byte boundary, so those shapes take the lane-per-channel kernel.
-bool use_chunked_full(const ScanArgs& a) {
-    return a.N == 16 && a.L > kShortMaxL && !(a.in_dt == VMB_BF16 && (a.L & 1));
+bool use_chunked_full(const ScanArgs& a) { return a.N == 16 && a.L > kShortMaxL; }
+
+// bf16, N = 16: with enough rows to fill the chip but too few for the tile
+// kernel's 64-channel workgroups to, one wave per sequence is the fastest, since
+// its loads and stores are whole vectors where the chunked kernel's are single
+// elements. Measured (us, 2-D; chunked, short or tile kernel against rows):
+// 56x56, 192 channels: 768 rows 40 / 60, 1536 73 / 70, 6144 273 / 150, 24576
+// 765 / 531, 36864 928 / 785, 49152 1008 / 1039; 28x28: 1536 rows 40 / 22, 24576
+// 218 / 170; 14x14: 3072 rows 29 / 16; 7x7 (L = 49): 6144 rows 22 / 23. (fp32,
+// 56x56: 3072 rows 86 / 91, 12288 316 / 338: chunked.)
+bool use_rows_full(const ScanArgs& a) {
+    const int64_t rows = a.batch * a.K * a.channels;
+    return a.N == 16 && a.in_dt == VMB_BF16 && a.L > 64 && rows >= 1200 && rows < 49152 &&
+           a.batch <= 65535 && a.K <= 65535;
 }
 
 vmb_status launch_full_scan(const ScanArgs& a) {
     // the zero-order-hold B runs in the tile, positions-over-lanes and lane
     // kernels (not the short-sequence one: those shapes take the tile kernel)
     const bool zoh = (a.options & VMB_SCAN_ZOH) != 0;
+    if (!zoh && use_rows_full(a)) return launch_full_rows(a);
     const bool tiles =
         use_tiles_full(a) || (zoh && !use_chunked_full(a) && tiles_take(a));
     if (tiles || use_chunked_full(a) || (!zoh && use_short_full(a))) {
