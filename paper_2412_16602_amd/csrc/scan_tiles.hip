@@ -22,11 +22,18 @@
 //     with row-contiguous vectors.
 // Two workgroup barriers per tile; the next tile's delta / u loads, and one
 // load per B / C row segment that brings those lines into L2, are in flight
-// while the current tile is scanned.
+// while the current tile is scanned; they are kept as loaded and converted
+// where they are used, since a conversion beside a load waits for it.
+//
+// What bounds it: instruction issue. Per element a multiply (2.5 cycles a wave
+// on its SIMD), an exp2 (8.3), a multiply and an fma with a scalar operand
+// (4.3 each; 2.5-2.8 without) and an fma (2.8): 22 of the 36 measured at 128 x
+// 28x28, 384 channels, fp32. 128 x 56x56, 192 channels, bf16, 2-D step: 1634 us
+// with conversions beside the loads and one wait per half tile for B and C,
+// 1470 us as it is (fp32: unchanged, 165 us at 32 x 28x28, sequence layout).
 //
 // Workgroups are numbered so that those sharing a (batch, direction), and
 // therefore B and C, land on the same XCD and its L2.
-#include <type_traits>
 
 #include "vmb_internal.h"
 
@@ -34,87 +41,62 @@ namespace vmb {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kTileWaves = 4;                     // four states per wave
+constexpr int kStates = 16;
+constexpr int kTileWaves = 4;                     // four states per wave (eight waves of two: no faster)
 constexpr int kTileThreads = kTileWaves * kWave;  // 256
 constexpr int kTP = 16;                           // positions per tile
 constexpr int kStride = kTP + 1;                  // LDS row stride (words): conflict-free columns
 
-// Four consecutive elements of a row starting at p: vector load when vec
-// (16-byte fp32 / 8-byte bf16 aligned and all in range), else cnt guarded
-// element loads, the rest 0.
-__device__ __forceinline__ void load4(const float* p, float (&v)[4], bool vec, int cnt) {
-    if (vec) {
-        const float4 q = *reinterpret_cast<const float4*>(p);
-        v[0] = q.x;
-        v[1] = q.y;
-        v[2] = q.z;
-        v[3] = q.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = e < cnt ? p[e] : 0.0f;
-    }
+// P consecutive elements of a row as they lie in memory: one vector (of any
+// element alignment), converted where it is used, so that nothing waits for
+// it before.
+template <typename Tin, int P>
+struct Piece {
+    uint32_t w[P * static_cast<int>(sizeof(Tin)) / 4];
+};
+template <int P>
+__device__ __forceinline__ float piece_at(const Piece<float, P>& r, int e) {
+    return __uint_as_float(r.w[e]);
 }
-__device__ __forceinline__ void load4(const bf16_t* p, float (&v)[4], bool vec, int cnt) {
-    if (vec) {
-        const uint2 q = *reinterpret_cast<const uint2*>(p);
-        v[0] = __uint_as_float(q.x << 16);
-        v[1] = __uint_as_float(q.x & 0xffff0000u);
-        v[2] = __uint_as_float(q.y << 16);
-        v[3] = __uint_as_float(q.y & 0xffff0000u);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = e < cnt ? to_f32(p[e]) : 0.0f;
-    }
+template <int P>
+__device__ __forceinline__ float piece_at(const Piece<bf16_t, P>& r, int e) {
+    return __uint_as_float((e & 1) ? r.w[e / 2] & 0xffff0000u : r.w[e / 2] << 16);
 }
-
-template <bool kNt>
-__device__ __forceinline__ void store4(float* p, const float (&v)[4], bool vec, int cnt) {
-    if (vec) {
-        if constexpr (kNt)
-            store_out<true>(reinterpret_cast<float4*>(p), make_float4(v[0], v[1], v[2], v[3]));
-        else
-            *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-    } else {
+template <bool kNt, typename Tout, int P>
+__device__ __forceinline__ void store_piece(Tout* p, const float (&v)[P]) {
+    struct alignas(P * sizeof(Tout)) Out {
+        Tout e[P];
+    } o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e < cnt) p[e] = v[e];
-    }
-}
-template <bool kNt>
-__device__ __forceinline__ void store4(bf16_t* p, const float (&v)[4], bool vec, int cnt) {
-    if (vec) {
-        bf16_t o[4] = {from_f32<bf16_t>(v[0]), from_f32<bf16_t>(v[1]), from_f32<bf16_t>(v[2]),
-                       from_f32<bf16_t>(v[3])};
-        if constexpr (kNt) {
-            unsigned long long q;
-            __builtin_memcpy(&q, o, sizeof(o));
-            store_out<true>(reinterpret_cast<unsigned long long*>(p), q);
-        } else {
-            __builtin_memcpy(p, o, sizeof(o));
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e < cnt) p[e] = from_f32<bf16_t>(v[e]);
-    }
+    for (int e = 0; e < P; ++e) o.e[e] = from_f32<Tout>(v[e]);
+    if constexpr (kNt)
+        store_out<true>(reinterpret_cast<Out*>(p), o);
+    else
+        __builtin_memcpy(p, &o, sizeof(o));
 }
 
-// Eight consecutive elements of a wave-uniform B or C row from element
-// offset off (scalar loads). bf16: off is even (even L, even tile starts),
-// so the elements are four whole 32-bit words.
-__device__ __forceinline__ void row8(const float* r, int off, float (&v)[8]) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = r[off + e];
+// Four consecutive positions of a wave's S B rows and S C rows, as they lie in
+// memory (scalar loads of whole 32-bit words: bf16 rows have even length,
+// and quarters start at even positions).
+template <typename Tin, int S>
+struct Quarter {
+    static constexpr int kWords = static_cast<int>(sizeof(Tin));  // 4 elements of a row
+    uint32_t b[S][kWords], c[S][kWords];
+};
+template <typename Tin>
+__device__ __forceinline__ float word_value(const uint32_t* w, int e);
+template <>
+__device__ __forceinline__ float word_value<float>(const uint32_t* w, int e) {
+    return __uint_as_float(w[e]);
 }
-__device__ __forceinline__ void row8(const bf16_t* r, int off, float (&v)[8]) {
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(r) + (off >> 1);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t x = w[q];
-        v[2 * q] = __uint_as_float(x << 16);
-        v[2 * q + 1] = __uint_as_float(x & 0xffff0000u);
-    }
+template <>
+__device__ __forceinline__ float word_value<bf16_t>(const uint32_t* w, int e) {
+    return __uint_as_float((e & 1) ? w[e / 2] & 0xffff0000u : w[e / 2] << 16);
 }
+
+// Wait for this wave's scalar loads and LDS operations (lgkmcnt(0), other
+// counters untouched).
+__device__ __forceinline__ void wait_lgkm() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 
 template <typename Tin, typename Tout, bool kTwoD, bool kZoh, bool kNt>
 __global__ __launch_bounds__(kTileThreads) void k_full_scan_tiles(
@@ -122,7 +104,10 @@ __global__ __launch_bounds__(kTileThreads) void k_full_scan_tiles(
     const Tin* __restrict__ Bm, const Tin* __restrict__ Cm, const float* __restrict__ D,
     const float* __restrict__ dt_bias, Tout* __restrict__ y, const Tin* __restrict__ xt, int K,
     int Dc, int L, int H, int W, int softplus, int n_cg, int n_wg) {
-    constexpr int N = 16;
+    constexpr int N = kStates;
+    constexpr int S = N / kTileWaves;              // states per wave
+    constexpr int P = kWave * kTP / kTileThreads;  // positions a thread loads and stores
+    constexpr int kPieces = kTP / P;               // threads per row
     __shared__ float s_dl2[kWave][kStride];               // Delta * log2 e
     __shared__ float s_du[kWave][kStride];                // Delta * u
     __shared__ float s_y[kTileWaves][kWave][kStride];     // per wave: its states' C h
@@ -144,8 +129,8 @@ __global__ __launch_bounds__(kTileThreads) void k_full_scan_tiles(
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const bool sp = softplus != 0;
 
-    // Loader role: row lr (channel d0 + lr), positions 4 lq .. 4 lq + 3 of each tile.
-    const int lr = tid >> 2, lq = tid & 3;
+    // Loader role: row lr (channel d0 + lr), positions P lq .. P lq + P - 1 of each tile.
+    const int lr = tid / kPieces, lq = tid % kPieces;
     const bool ld_ok = d0 + lr < Dc;
     const int ld_d = ld_ok ? d0 + lr : Dc - 1;  // rows past the end repeat a valid one, unstored
     const int ld_c = k * Dc + ld_d;
@@ -160,22 +145,18 @@ __global__ __launch_bounds__(kTileThreads) void k_full_scan_tiles(
     const Tin* srow = (kTwoD && (k & 1) && xt) ? xt + (static_cast<size_t>(b) * Dc + ld_d) * L : urow;
     const bool gather = kTwoD && (k & 1) && !xt;
     Tout* yrow = y + ld_row;
-    // every row starts on a 4-element boundary: 4-element pieces are 16-byte
-    // (fp32) or 8-byte (bf16) aligned vectors
-    const bool in_aligned = (L % 4) == 0;
-
-    // Scan role: lane = channel d0 + lane, states 4 wv .. 4 wv + 3.
+    // Scan role: lane = channel d0 + lane, states S wv .. S wv + S - 1.
     const int sd = d0 + lane < Dc ? d0 + lane : Dc - 1;
     const int sc = k * Dc + sd;
-    float an[4], h[4], inv_a[4];
+    float an[S], h[S], inv_a[S];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        an[j] = A[static_cast<size_t>(sc) * N + 4 * wv + j];
+    for (int j = 0; j < S; ++j) {
+        an[j] = A[static_cast<size_t>(sc) * N + S * wv + j];
         inv_a[j] = kZoh ? 1.0f / an[j] : 0.0f;
         h[j] = 0.0f;
     }
-    // the wave's four B and C rows: one base each, rows L elements apart
-    const size_t r0 = (static_cast<size_t>(bk) * N + 4 * wv) * static_cast<size_t>(L);
+    // the wave's B and C rows: one base each, rows L elements apart
+    const size_t r0 = (static_cast<size_t>(bk) * N + S * wv) * static_cast<size_t>(L);
     const Tin* bbase = Bm + r0;
     const Tin* cbase = Cm + r0;
 
@@ -185,117 +166,178 @@ __global__ __launch_bounds__(kTileThreads) void k_full_scan_tiles(
     // as identity steps (Delta = 0: a = 1, b = 0) and not stored again.
     const int ntiles = (L + kTP - 1) / kTP;
     auto tile_start = [&](int tile) { return tile * kTP + kTP <= L ? tile * kTP : L - kTP; };
-    float dv[4], uv[4];
+    Piece<Tin, P> dv, uv;
+    const bool reversed = kTwoD && !gather && k >= 2;  // uv holds the piece back to front
     auto load_tile = [&](int tile) {
-        const int t = tile_start(tile) + 4 * lq;
-        load4(drow + t, dv, in_aligned, 4);
+        const int t = tile_start(tile) + P * lq;
+        __builtin_memcpy(&dv, drow + t, sizeof(dv));
         if constexpr (kTwoD) {
             if (gather) {
+                Tin e[P];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) uv[e] = to_f32(urow[pixel_of(k, t + e, H, W)]);
-            } else if (k < 2) {
-                load4(srow + t, uv, in_aligned, 4);
+                for (int i = 0; i < P; ++i) e[i] = urow[pixel_of(k, t + i, H, W)];
+                __builtin_memcpy(&uv, e, sizeof(uv));
             } else {
-                float r[4];
-                load4(srow + (L - 4 - t), r, in_aligned, 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) uv[e] = r[3 - e];
+                __builtin_memcpy(&uv, srow + (k < 2 ? t : L - P - t), sizeof(uv));
             }
         } else {
-            load4(urow + t, uv, in_aligned, 4);
+            __builtin_memcpy(&uv, urow + t, sizeof(uv));
         }
     };
     load_tile(0);
     // L2 prefetch of the next tile's B and C segments (16 + 16 rows of the
     // direction, one line each), so that the scan's scalar loads of them do
     // not wait for HBM: threads 0..31 each touch one row and hold the value
-    // until the following tile, where it is consumed (a precise vmcnt wait
-    // long after the load completed).
+    // until step 4.
     const Tin* pf_row = (tid < 16 ? Bm : Cm) +
                         (static_cast<size_t>(bk) * N + (tid & 15)) * static_cast<size_t>(L);
-    float pf = 0.0f;
+    uint32_t pf = 0;  // raw bits: a conversion would wait for the load
+    Quarter<Tin, S> bc[2];
+    auto load_bc = [&](Quarter<Tin, S>& r, int off) {
+        constexpr int kPer = 4 / static_cast<int>(sizeof(Tin));  // elements per word
+        // opaque: the quarters' loads are not merged into wider ones, which
+        // would all be needed (and held) at once
+        unsigned first = static_cast<unsigned>(off) / kPer;
+        asm volatile("" : "+s"(first));
+        const uint32_t* bq = reinterpret_cast<const uint32_t*>(bbase) + first;
+        const uint32_t* cq = reinterpret_cast<const uint32_t*>(cbase) + first;
+        const unsigned words = static_cast<unsigned>(L) / kPer;  // of a row
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+            const uint32_t* bw = bq + static_cast<size_t>(j) * words;
+            const uint32_t* cw = cq + static_cast<size_t>(j) * words;
+#pragma unroll
+            for (int w = 0; w < Quarter<Tin, S>::kWords; ++w) {
+                r.b[j][w] = bw[w];
+                r.c[j][w] = cw[w];
+            }
+        }
+    };
+    load_bc(bc[0], tile_start(0));
 
     for (int tile = 0; tile < ntiles; ++tile) {
         const int t0 = tile_start(tile);
         const int tnew = tile * kTP;  // positions below tnew belong to the previous tile
-        // 1. discretize this thread's four positions
-        float skip[4];
+        // 1. discretize this thread's P positions
+        float skip[P];
         {
-            const int t = t0 + 4 * lq;
+            const int t = t0 + P * lq;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float dl = t + e >= tnew ? timescale(dv[e] + ld_bias, sp) : 0.0f;
-                s_dl2[lr][4 * lq + e] = dl * kLog2e;
-                s_du[lr][4 * lq + e] = dl * uv[e];
-                if constexpr (kZoh) s_u[lr][4 * lq + e] = uv[e];
-                skip[e] = ld_skip * uv[e];
+            for (int e = 0; e < P; ++e) {
+                const float d = piece_at<P>(dv, e);
+                const float ut = reversed ? piece_at<P>(uv, P - 1 - e) : piece_at<P>(uv, e);
+                const float dl = t + e >= tnew ? timescale(d + ld_bias, sp) : 0.0f;
+                s_dl2[lr][P * lq + e] = dl * kLog2e;
+                s_du[lr][P * lq + e] = dl * ut;
+                if constexpr (kZoh) s_u[lr][P * lq + e] = ut;
+                skip[e] = ld_skip * ut;
             }
         }
         __syncthreads();
         // 2. the next tile's delta / u (and its B, C lines), in flight during the scan
         if (tile + 1 < ntiles) {
             load_tile(tile + 1);
-            asm volatile("" ::"v"(pf));
-            if (tid < 2 * N) pf = to_f32(pf_row[tile_start(tile + 1)]);
+            if (tid < 2 * N) {
+                const Tin* line = pf_row + tile_start(tile + 1);
+                if constexpr (sizeof(Tin) == 4)
+                    pf = *reinterpret_cast<const uint32_t*>(line);
+                else
+                    pf = *reinterpret_cast<const uint16_t*>(line);
+            }
         }
-        // 3. scan the tile: four recurrences per lane, straight along the
-        //    positions, in two halves of 8. Each half first issues all its B
-        //    and C scalar loads (4 states x 8 consecutive positions each) and
-        //    waits once: scalar loads complete out of order, so every wait is
-        //    for all of them.
-        float yp[kTP];
+        // 3. scan the tile: S recurrences per lane, straight along the
+        //    positions, in quarters of 4. Scalar loads complete out of order,
+        //    so every wait is for all of them (and for LDS, which counts with
+        //    them): a quarter's B, C, Delta and Delta u are waited for once,
+        //    before the next quarter's are requested, and those are in flight
+        //    during its arithmetic (the first quarter of the next tile's B
+        //    and C during the last one's).
+        float yp[kTP], xd[2][4], xu[2][4], xi[2][4];
+        auto read_lds = [&](int q) {
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            float bq[4][kTP / 2], cq[4][kTP / 2];
+            for (int e = 0; e < 4; ++e) {
+                xd[q & 1][e] = s_dl2[lane][4 * q + e];
+                xu[q & 1][e] = s_du[lane][4 * q + e];
+                xi[q & 1][e] = kZoh ? s_u[lane][4 * q + e] : 0.0f;
+            }
+        };
+        read_lds(0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                row8(bbase, j * L + t0 + 8 * hh, bq[j]);
-                row8(cbase, j * L + t0 + 8 * hh, cq[j]);
+        for (int q = 0; q < 4; ++q) {
+            wait_lgkm();
+            __builtin_amdgcn_sched_barrier(0);
+            if (q < 3) {
+                load_bc(bc[(q + 1) & 1], t0 + 4 * (q + 1));
+                read_lds(q + 1);
+            } else {
+                load_bc(bc[0], tile_start(tile + 1 < ntiles ? tile + 1 : tile));
             }
             __builtin_amdgcn_sched_barrier(0);
+            const Quarter<Tin, S>& cur = bc[q & 1];
 #pragma unroll
-            for (int e = 0; e < kTP / 2; ++e) {
-                const int i = 8 * hh + e;
-                const float dl2 = s_dl2[lane][i];
-                const float du = s_du[lane][i];
-                const float ui = kZoh ? s_u[lane][i] : 0.0f;
+            for (int e = 0; e < 4; ++e) {
+                const float dl2 = xd[q & 1][e], du = xu[q & 1][e], ui = xi[q & 1][e];
                 float acc = 0.0f;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < S; ++j) {
                     const float x2 = dl2 * an[j];
                     const float a = fast_exp2(x2);
-                    const float q = kZoh ? zoh_q(x2, a, du, ui, inv_a[j]) : du;
-                    h[j] = __builtin_fmaf(a, h[j], q * bq[j][e]);
-                    acc = __builtin_fmaf(cq[j][e], h[j], acc);
+                    const float qb = kZoh ? zoh_q(x2, a, du, ui, inv_a[j]) : du;
+                    h[j] = __builtin_fmaf(a, h[j], qb * word_value<Tin>(cur.b[j], e));
+                    acc = __builtin_fmaf(word_value<Tin>(cur.c[j], e), h[j], acc);
                 }
-                yp[i] = acc;
+                yp[4 * q + e] = acc;
             }
         }
 #pragma unroll
         for (int i = 0; i < kTP; ++i) s_y[wv][lane][i] = yp[i];
         __syncthreads();
         // 4. y = D u + the four waves' partial sums, stored row-contiguous
-        //    (a piece that straddles the previous tile stores its new part)
-        {
-            const int t = t0 + 4 * lq;
-            float o[4];
+        //    (a piece that straddles the previous tile stores its new part).
+        //    The next tile's loads are waited for here, ahead of the stores:
+        //    vector-memory operations retire in order, and waited for after
+        //    them they would wait for the stores as well.
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 4 * lq + e;
-                o[e] = skip[e] + ((s_y[0][lr][i] + s_y[1][lr][i]) + (s_y[2][lr][i] + s_y[3][lr][i]));
+        for (uint32_t& x : dv.w) asm volatile("" : "+v"(x));
+#pragma unroll
+        for (uint32_t& x : uv.w) asm volatile("" : "+v"(x));
+        asm volatile("" : "+v"(pf));
+        {
+            const int t = t0 + P * lq;
+            float o[P];
+#pragma unroll
+            for (int e = 0; e < P; ++e) {
+                const int i = P * lq + e;
+                float part[kTileWaves];  // summed in pairs, in wave order
+#pragma unroll
+                for (int w = 0; w < kTileWaves; ++w) part[w] = s_y[w][lr][i];
+#pragma unroll
+                for (int n = kTileWaves; n > 1; n /= 2)
+#pragma unroll
+                    for (int w = 0; w < n / 2; ++w) part[w] = part[2 * w] + part[2 * w + 1];
+                o[e] = skip[e] + part[0];
             }
             if (ld_ok) {
                 if (t >= tnew) {
-                    store4<kNt>(yrow + t, o, in_aligned, 4);
+                    store_piece<kNt>(yrow + t, o);
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (t + e >= tnew)
-                            store4<false>(yrow + t + e, {o[e], 0.0f, 0.0f, 0.0f}, false, 1);
+                    for (int e = 0; e < P; ++e)
+                        if (t + e >= tnew) yrow[t + e] = from_f32<Tout>(o[e]);
                 }
             }
         }
     }
+}
+
+template <typename Tin, typename Tout, bool kTwoD, bool kZoh, bool kNt>
+void launch_tiles_kernel(const ScanArgs& a, Tout* y, const void* xt, int n_cg, int n_wg) {
+    hipLaunchKernelGGL((k_full_scan_tiles<Tin, Tout, kTwoD, kZoh, kNt>),
+                       dim3(static_cast<unsigned>(n_wg)), dim3(kTileThreads), 0, a.stream,
+                       static_cast<const Tin*>(a.u), static_cast<const Tin*>(a.delta), a.A,
+                       static_cast<const Tin*>(a.B), static_cast<const Tin*>(a.C), a.D, a.dt_bias,
+                       y, static_cast<const Tin*>(xt), int(a.K), int(a.channels), int(a.L),
+                       int(a.H), int(a.W), a.softplus, n_cg, n_wg);
 }
 
 template <typename Tin, typename Tout, bool kTwoD, bool kZoh>
@@ -304,20 +346,12 @@ vmb_status launch_tiles_zoh(const ScanArgs& a, Tout* y, const void* xt) {
     const long long n_wg = static_cast<long long>(n_cg) * a.K * a.batch;
     if (n_wg > 0x7fffffffLL) return VMB_ERR_UNSUPPORTED;
     // non-temporal output stores for rows of whole cache lines
-    if (whole_lines(a.L, sizeof(Tout)))
-        hipLaunchKernelGGL((k_full_scan_tiles<Tin, Tout, kTwoD, kZoh, true>),
-                           dim3(static_cast<unsigned>(n_wg)), dim3(kTileThreads), 0, a.stream,
-                           static_cast<const Tin*>(a.u), static_cast<const Tin*>(a.delta), a.A,
-                           static_cast<const Tin*>(a.B), static_cast<const Tin*>(a.C), a.D,
-                           a.dt_bias, y, static_cast<const Tin*>(xt), int(a.K), int(a.channels),
-                           int(a.L), int(a.H), int(a.W), a.softplus, n_cg, int(n_wg));
+    const bool nt = whole_lines(a.L, sizeof(Tout));
+    const int g = int(n_wg);
+    if (nt)
+        launch_tiles_kernel<Tin, Tout, kTwoD, kZoh, true>(a, y, xt, n_cg, g);
     else
-        hipLaunchKernelGGL((k_full_scan_tiles<Tin, Tout, kTwoD, kZoh, false>),
-                           dim3(static_cast<unsigned>(n_wg)), dim3(kTileThreads), 0, a.stream,
-                           static_cast<const Tin*>(a.u), static_cast<const Tin*>(a.delta), a.A,
-                           static_cast<const Tin*>(a.B), static_cast<const Tin*>(a.C), a.D,
-                           a.dt_bias, y, static_cast<const Tin*>(xt), int(a.K), int(a.channels),
-                           int(a.L), int(a.H), int(a.W), a.softplus, n_cg, int(n_wg));
+        launch_tiles_kernel<Tin, Tout, kTwoD, kZoh, false>(a, y, xt, n_cg, g);
     return check_launch();
 }
 
