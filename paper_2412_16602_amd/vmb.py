@@ -114,6 +114,9 @@ _DT = {torch.float32: VMB_F32, torch.bfloat16: VMB_BF16}
 
 
 def _dev(t: Optional[torch.Tensor], name: str):
+    """Device address of a contiguous GPU tensor, or None. A plain integer: the
+    declared argument types make the pointer of it, without an object in
+    between (a scan call passes nine of them)."""
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
@@ -122,13 +125,14 @@ def _dev(t: Optional[torch.Tensor], name: str):
         raise ValueError(f"{name} must be a GPU tensor (got {t.device})")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dtype(t: torch.Tensor, name: str) -> int:
-    if t.dtype not in _DT:
+    dt = _DT.get(t.dtype)
+    if dt is None:
         raise ValueError(f"{name}: unsupported dtype {t.dtype}")
-    return _DT[t.dtype]
+    return dt
 
 
 def _f32(t: Optional[torch.Tensor], name: str):
@@ -137,10 +141,17 @@ def _f32(t: Optional[torch.Tensor], name: str):
     return _dev(t, name)
 
 
-def _stream(stream) -> ctypes.c_void_p:
+# The current stream's handle of a device, without the Stream object that
+# torch.cuda.current_stream() builds around it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(stream.cuda_stream))
+    return int(stream.cuda_stream)
 
 
 def _check(status: int, where: str):
@@ -157,7 +168,7 @@ def vmb_cross_scan(x: torch.Tensor, xs: torch.Tensor, stream=None) -> torch.Tens
     dt = _dtype(x, "x")
     if xs.dtype != x.dtype:
         raise ValueError("xs must have the dtype of x")
-    if tuple(xs.shape) != (batch, 4, channels, H * W):
+    if xs.shape != (batch, 4, channels, H * W):
         raise ValueError(f"xs shape {tuple(xs.shape)} != {(batch, 4, channels, H * W)}")
     _check(lib.vmb_cross_scan(_dev(x, "x"), _dev(xs, "xs"), batch, channels, H, W, dt,
                               _stream(stream)), "vmb_cross_scan")
@@ -171,7 +182,7 @@ def vmb_cross_merge(ys: torch.Tensor, y: torch.Tensor, stream=None) -> torch.Ten
     dt = _dtype(ys, "ys")
     if y.dtype != ys.dtype:
         raise ValueError("y must have the dtype of ys")
-    if tuple(ys.shape) != (batch, 4, channels, H * W):
+    if ys.shape != (batch, 4, channels, H * W):
         raise ValueError(f"ys shape {tuple(ys.shape)} != {(batch, 4, channels, H * W)}")
     _check(lib.vmb_cross_merge(_dev(ys, "ys"), _dev(y, "y"), batch, channels, H, W, dt,
                                _stream(stream)), "vmb_cross_merge")
@@ -186,31 +197,33 @@ def vmb_scan_workspace_bytes(mean_variant: bool, batch: int, K: int, channels: i
 
 def _scan(name, mean_variant, u, delta, A, B, C, D, dt_bias, delta_softplus, y, layout,
           workspace, stream, options=None):
-    lib = load_library()
+    lib = _lib or load_library()
     batch, K, channels, L = delta.shape
     N = A.shape[1]
+    dtype = delta.dtype
     in_dt = _dtype(delta, "delta")
     out_dt = _dtype(y, "y")
     for t, nm in ((u, "u"), (B, "B"), (C, "C")):
-        if t.dtype != delta.dtype:
+        if t.dtype != dtype:
             raise ValueError(f"{nm} must have the dtype of delta")
     if layout == VMB_LAYOUT_2D:
         if u.dim() != 4 or u.shape[0] != batch or u.shape[1] != channels:
             raise ValueError("2-D layout: u must be x [batch, channels, H, W]")
-        H, W = int(u.shape[2]), int(u.shape[3])
+        H, W = u.shape[2], u.shape[3]
         y_shape = (batch, channels, H, W)
     else:
         H, W = 1, L
-        if tuple(u.shape) != (batch, K, channels, L):
+        if u.shape != (batch, K, channels, L):
             raise ValueError(f"u shape {tuple(u.shape)} != {(batch, K, channels, L)}")
         rows = 1 if options and options & VMB_MEAN_NO_BROADCAST else channels
         y_shape = (batch, K, rows, L)
-    if tuple(y.shape) != y_shape:
+    if y.shape != y_shape:
         raise ValueError(f"y shape {tuple(y.shape)} != {y_shape}")
+    bc_shape = (batch, K, N, L)
     for t, nm in ((B, "B"), (C, "C")):
-        if tuple(t.shape) != (batch, K, N, L):
-            raise ValueError(f"{nm} shape {tuple(t.shape)} != {(batch, K, N, L)}")
-    if tuple(A.shape) != (K * channels, N):
+        if t.shape != bc_shape:
+            raise ValueError(f"{nm} shape {tuple(t.shape)} != {bc_shape}")
+    if A.shape != (K * channels, N):
         raise ValueError(f"A shape {tuple(A.shape)} != {(K * channels, N)}")
     for t, nm in ((D, "D"), (dt_bias, "dt_bias")):
         if t is not None and t.numel() != K * channels:
@@ -224,11 +237,12 @@ def _scan(name, mean_variant, u, delta, A, B, C, D, dt_bias, delta_softplus, y, 
             workspace = (torch.empty(max(need, 1), dtype=torch.uint8, device=delta.device)
                          if need else None)
         ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-        args += [_dev(workspace, "workspace"), ws_bytes]
+        args += (_dev(workspace, "workspace"), ws_bytes)
     if options is not None:
         args.append(int(options))
     status = getattr(lib, name)(*args, _stream(stream))
-    _check(status, name)
+    if status != 0:
+        raise VmbError(status, name)
     return y
 
 
@@ -292,14 +306,14 @@ def vmb_ss2d_projections(u: torch.Tensor, W: torch.Tensor, W_dt: Optional[torch.
     batch, K, channels, L = u.shape
     N = B.shape[2]
     R = W.shape[1] - 2 * N
-    if tuple(W.shape) != (K, R + 2 * N, channels):
+    if W.shape != (K, R + 2 * N, channels):
         raise ValueError(f"W shape {tuple(W.shape)} != {(K, R + 2 * N, channels)}")
-    if W_dt is not None and tuple(W_dt.shape) != (K, channels, R):
+    if W_dt is not None and W_dt.shape != (K, channels, R):
         raise ValueError(f"W_dt shape {tuple(W_dt.shape)} != {(K, channels, R)}")
-    if tuple(delta.shape) != tuple(u.shape):
+    if delta.shape != u.shape:
         raise ValueError("delta must have the shape of u")
     for t, nm in ((B, "B"), (C, "C")):
-        if tuple(t.shape) != (batch, K, N, L):
+        if t.shape != (batch, K, N, L):
             raise ValueError(f"{nm} shape {tuple(t.shape)} != {(batch, K, N, L)}")
     for t, nm in ((delta, "delta"), (B, "B"), (C, "C")):
         if t.dtype != u.dtype:
@@ -322,7 +336,7 @@ def vmb_ss2d_out_norm(y: torch.Tensor, z: Optional[torch.Tensor], gamma: Optiona
     if y.dim() < 3 or batch * channels * P != y.numel():
         raise ValueError(f"y shape {tuple(y.shape)} is not [batch, channels, ...]")
     for t, nm in ((z, "z"), (out, "out")):
-        if t is not None and (tuple(t.shape) != tuple(y.shape) or t.dtype != y.dtype):
+        if t is not None and (t.shape != y.shape or t.dtype != y.dtype):
             raise ValueError(f"{nm} must have the shape and dtype of y")
     for t, nm in ((gamma, "gamma"), (beta, "beta")):
         if t is not None and t.numel() != channels:
@@ -344,9 +358,9 @@ def vmb_discrete_scan(abar: torch.Tensor, bu: torch.Tensor, C: torch.Tensor,
     lib = load_library()
     batch, channels, L = abar.shape
     for t, name in ((bu, "bu"), (y, "y")) + (((skip, "skip"),) if skip is not None else ()):
-        if tuple(t.shape) != (batch, channels, L):
+        if t.shape != (batch, channels, L):
             raise ValueError(f"{name} shape {tuple(t.shape)} != {(batch, channels, L)}")
-    if tuple(C.shape) != (batch, L):
+    if C.shape != (batch, L):
         raise ValueError(f"C shape {tuple(C.shape)} != {(batch, L)}")
     _check(lib.vmb_discrete_scan(_f32(abar, "abar"), _f32(bu, "bu"), _f32(C, "C"),
                                  _f32(skip, "skip"), _f32(y, "y"), batch, channels, L,
@@ -358,7 +372,7 @@ def vmb_channel_mean(x: torch.Tensor, xm: torch.Tensor, stream=None) -> torch.Te
     """T of eq. 9: x [batch, channels, L] -> xm [batch, L], the channel mean (float32)."""
     lib = load_library()
     batch, channels, L = x.shape
-    if tuple(xm.shape) != (batch, L):
+    if xm.shape != (batch, L):
         raise ValueError(f"xm shape {tuple(xm.shape)} != {(batch, L)}")
     _check(lib.vmb_channel_mean(_f32(x, "x"), _f32(xm, "xm"), batch, channels, L,
                                 _stream(stream)), "vmb_channel_mean")
