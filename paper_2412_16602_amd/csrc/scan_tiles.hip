@@ -30,7 +30,9 @@
 // (4.3 each; 2.5-2.8 without) and an fma (2.8): 22 of the 36 measured at 128 x
 // 28x28, 384 channels, fp32. 128 x 56x56, 192 channels, bf16, 2-D step: 1634 us
 // with conversions beside the loads and one wait per half tile for B and C,
-// 1470 us as it is (fp32: unchanged, 165 us at 32 x 28x28, sequence layout).
+// 1480 us without (fp32: unchanged, 166 us at 32 x 28x28, sequence layout), and
+// 1460 and 163 us with a select in place of a divergent branch around each
+// position's softplus.
 //
 // Workgroups are numbered so that those sharing a (batch, direction), and
 // therefore B and C, land on the same XCD and its L2.
@@ -222,11 +224,19 @@ __global__ __launch_bounds__(kTileThreads) void k_full_scan_tiles(
         float skip[P];
         {
             const int t = t0 + P * lq;
+            // one uniform branch and a select, no branch per position: the
+            // positions' softplus chains interleave
+            float step[P];
+#pragma unroll
+            for (int e = 0; e < P; ++e) step[e] = piece_at<P>(dv, e) + ld_bias;
+            if (sp) {
+#pragma unroll
+                for (int e = 0; e < P; ++e) step[e] = timescale(step[e], true);
+            }
 #pragma unroll
             for (int e = 0; e < P; ++e) {
-                const float d = piece_at<P>(dv, e);
                 const float ut = reversed ? piece_at<P>(uv, P - 1 - e) : piece_at<P>(uv, e);
-                const float dl = t + e >= tnew ? timescale(d + ld_bias, sp) : 0.0f;
+                const float dl = t + e >= tnew ? step[e] : 0.0f;
                 s_dl2[lr][P * lq + e] = dl * kLog2e;
                 s_du[lr][P * lq + e] = dl * ut;
                 if constexpr (kZoh) s_u[lr][P * lq + e] = ut;
