@@ -12,7 +12,9 @@
 // through a padded copy of the plane in LDS (row stride W + 1 words, so the
 // column walk is free of bank conflicts). Every global access is a full
 // 16-byte vector of consecutive elements. Larger planes use 32 x 32 pixel
-// tiles (blockDim 32 x 8) with an LDS transpose for the column directions.
+// tiles (blockDim 32 x 8) with an LDS transpose for the column directions, or,
+// for the merge and the column-major copies of planes whose rows and columns
+// are whole vectors, 64 x 64 tiles of vectors.
 #include "vmb_internal.h"
 
 namespace vmb {
@@ -450,6 +452,19 @@ __global__ __launch_bounds__(256) void k_transpose_vec(const T* __restrict__ x, 
     }
 }
 
+// Whether rows, columns and pointers are whole vectors of V elements.
+template <int V>
+bool whole_vectors(const void* a, const void* b, int64_t H, int64_t W) {
+    return H % V == 0 && W % V == 0 &&
+           ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0;
+}
+
+static dim3 vec_tile_grid(int64_t batch, int64_t channels, int64_t H, int64_t W) {
+    return dim3(static_cast<unsigned>(batch * channels),
+                static_cast<unsigned>((H + kVTile - 1) / kVTile),
+                static_cast<unsigned>((W + kVTile - 1) / kVTile));
+}
+
 vmb_status launch_transpose_planes(const void* x, void* xt, int64_t batch, int64_t channels,
                                    int64_t H, int64_t W, vmb_dtype dt, hipStream_t s) {
     if (plane_fits(batch, channels, H, W))
@@ -457,13 +472,8 @@ vmb_status launch_transpose_planes(const void* x, void* xt, int64_t batch, int64
     // planes beyond LDS: 32 x 32 tiles
     if (!grid_fits(batch, channels, H, W)) return VMB_ERR_UNSUPPORTED;
     // vectors where every row and column is made of whole, aligned ones
-    const int64_t per = dt == VMB_F32 ? 4 : 8;
-    const bool aligned =
-        ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(xt)) & 15) == 0;
-    if (aligned && H % per == 0 && W % per == 0) {
-        const dim3 g(static_cast<unsigned>(batch * channels),
-                     static_cast<unsigned>((H + kVTile - 1) / kVTile),
-                     static_cast<unsigned>((W + kVTile - 1) / kVTile));
+    if (dt == VMB_F32 ? whole_vectors<4>(x, xt, H, W) : whole_vectors<8>(x, xt, H, W)) {
+        const dim3 g = vec_tile_grid(batch, channels, H, W);
         if (dt == VMB_F32)
             hipLaunchKernelGGL((k_transpose_vec<float>), g, dim3(256), 0, s,
                                static_cast<const float*>(x), static_cast<float*>(xt), int(H),
@@ -580,6 +590,83 @@ void launch_merge_plane(const void* ys, void* y, int64_t batch, int64_t channels
         launch_merge_tpp<Tin, Tout, 1>(in, out, batch * channels, c, h, w, s);
 }
 
+// The merge of planes beyond LDS whose rows and columns are whole vectors, by
+// 64 x 64 tiles as in k_transpose_vec: y1 + y3 is formed in column order,
+// parked, and added to y0 + y2 in row order (every load a vector of V
+// elements, where k_cross_merge takes one element a lane).
+// 2 x 192 planes of 128 x 512: fp32 104 -> 94 us (5.4 TB/s), bf16 output 103 -> 87.
+template <typename Tin, typename Tout, int V>
+__global__ __launch_bounds__(256) void k_cross_merge_vec(const Tin* __restrict__ ys,
+                                                         Tout* __restrict__ y, int Dc, int H,
+                                                         int W) {
+    constexpr int kVecs = kVTile / V;
+    constexpr int kStep = 256 / kVecs;
+    constexpr int kPasses = kVTile / kStep;
+    __shared__ float s13[kVTile][kVTile + 1];
+    const size_t L = static_cast<size_t>(H) * W;
+    const int plane = blockIdx.x;
+    const int b = plane / Dc;
+    const int d = plane - b * Dc;
+    const int h0 = blockIdx.y * kVTile, w0 = blockIdx.z * kVTile;
+    const int r = threadIdx.x / kVecs, c = threadIdx.x % kVecs * V;
+    const Tin* in0 = ys + (static_cast<size_t>(b) * 4 * Dc + d) * L;
+    const Tin* in1 = in0 + Dc * L;
+    const Tin* in2 = in1 + Dc * L;
+    const Tin* in3 = in2 + Dc * L;
+    Vec<Tin, V> a0[kPasses], a1[kPasses], a2[kPasses], a3[kPasses];
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int w = w0 + r + i * kStep, h = h0 + c;
+        if (h < H && w < W) {
+            const size_t q = static_cast<size_t>(w) * H + h;
+            a1[i] = load_vec<Tin, V>(in1 + q);
+            a3[i] = load_vec<Tin, V>(in3 + (L - V - q));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int h = h0 + r + i * kStep, w = w0 + c;
+        if (h < H && w < W) {
+            const size_t p = static_cast<size_t>(h) * W + w;
+            a0[i] = load_vec<Tin, V>(in0 + p);
+            a2[i] = load_vec<Tin, V>(in2 + (L - V - p));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i)
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            s13[c + e][r + i * kStep] = to_f32(a1[i].v[e]) + to_f32(a3[i].v[V - 1 - e]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int h = h0 + r + i * kStep, w = w0 + c;
+        if (h < H && w < W) {
+            Vec<Tout, V> o;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const float s02 = to_f32(a0[i].v[e]) + to_f32(a2[i].v[V - 1 - e]);
+                o.v[e] = from_f32<Tout>(s02 + s13[r + i * kStep][c + e]);
+            }
+            store_vec<Tout, V>(y + static_cast<size_t>(plane) * L + static_cast<size_t>(h) * W + w, o);
+        }
+    }
+}
+
+template <typename Tin, typename Tout>
+void launch_merge_tiles(const void* ys, void* y, int64_t batch, int64_t channels, int64_t H,
+                        int64_t W, hipStream_t s) {
+    constexpr int V = (sizeof(Tin) == 2 && sizeof(Tout) == 2) ? 8 : 4;
+    const Tin* in = static_cast<const Tin*>(ys);
+    Tout* out = static_cast<Tout*>(y);
+    if (whole_vectors<V>(ys, y, H, W))
+        hipLaunchKernelGGL((k_cross_merge_vec<Tin, Tout, V>), vec_tile_grid(batch, channels, H, W),
+                           dim3(256), 0, s, in, out, int(channels), int(H), int(W));
+    else
+        hipLaunchKernelGGL((k_cross_merge<Tin, Tout>), tile_grid(batch, channels, H, W),
+                           dim3(kTile, kRows), 0, s, in, out, int(channels), int(H), int(W));
+}
+
 vmb_status launch_cross_merge(const void* ys, void* y, int64_t batch, int64_t channels,
                               int64_t H, int64_t W, vmb_dtype in_dt, vmb_dtype out_dt,
                               hipStream_t s) {
@@ -606,17 +693,12 @@ vmb_status launch_cross_merge(const void* ys, void* y, int64_t batch, int64_t ch
         return check_launch();
     }
     if (!grid_fits(batch, channels, H, W)) return VMB_ERR_UNSUPPORTED;
-    const dim3 grid = tile_grid(batch, channels, H, W), block(kTile, kRows);
-    const int c = int(channels), h = int(H), w = int(W);
     if (in_dt == VMB_F32 && out_dt == VMB_F32)
-        hipLaunchKernelGGL((k_cross_merge<float, float>), grid, block, 0, s,
-                           static_cast<const float*>(ys), static_cast<float*>(y), c, h, w);
+        launch_merge_tiles<float, float>(ys, y, batch, channels, H, W, s);
     else if (in_dt == VMB_F32 && out_dt == VMB_BF16)
-        hipLaunchKernelGGL((k_cross_merge<float, bf16_t>), grid, block, 0, s,
-                           static_cast<const float*>(ys), static_cast<bf16_t*>(y), c, h, w);
+        launch_merge_tiles<float, bf16_t>(ys, y, batch, channels, H, W, s);
     else if (in_dt == VMB_BF16 && out_dt == VMB_BF16)
-        hipLaunchKernelGGL((k_cross_merge<bf16_t, bf16_t>), grid, block, 0, s,
-                           static_cast<const bf16_t*>(ys), static_cast<bf16_t*>(y), c, h, w);
+        launch_merge_tiles<bf16_t, bf16_t>(ys, y, batch, channels, H, W, s);
     else
         return VMB_ERR_DTYPE;
     return check_launch();

@@ -7,6 +7,7 @@ import torch
 import workloads
 from gpu_util import FP32_TOL, assert_close, dev, log, to_f64, upload_f32, upload_stream
 from paper_2412_16602_amd import vmb
+from test_gpu_cross import test_cross_merge_bit_exact as merge_bit_exact
 from test_gpu_scan import merged_oracle
 
 pytestmark = pytest.mark.gpu
@@ -27,3 +28,10 @@ def test_transpose_vec(H, W, dtype):
     ref, scale = merged_oracle(inp, "mean")
     assert_close(to_f64(y), ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
                  what=f"mean 2d {H}x{W} {dtype}")
+
+
+# the merge of such planes (bit-exact), by the same tiles
+@pytest.mark.parametrize("H,W", [(128, 128), (68, 196), (260, 60), (72, 200), (264, 56)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_merge_vec(H, W, dtype):
+    merge_bit_exact((2, 3, H, W), dtype)
