@@ -173,6 +173,103 @@ struct RowArgs {
     unsigned n_wg;  // whole grid, 0 when it is not renumbered
 };
 
+// Where a wave works: batch entry, direction, first channel, number of channels.
+struct Place {
+    int b, k, d0, nc;
+};
+// Workgroup i runs on XCD i % 8 (own L2): each XCD takes a contiguous
+// range, so the channels that share B and C rows share an L2.
+template <int kMode, int kPlanes>
+__device__ __forceinline__ Place place_of(const RowArgs& g) {
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int grp;
+    Place p;
+    if (g.n_wg) {
+        const unsigned bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+        const unsigned per = g.n_wg / 8, rem = g.n_wg % 8, xcd = bid % 8, slot = bid / 8;
+        unsigned id = xcd * per + (xcd < rem ? xcd : rem) + slot;
+        grp = static_cast<int>(id % static_cast<unsigned>(g.groups));
+        id /= static_cast<unsigned>(g.groups);
+        p.k = static_cast<int>(id % gridDim.y);
+        p.b = static_cast<int>(id / gridDim.y);
+    } else {
+        grp = blockIdx.x;
+        p.k = blockIdx.y;
+        p.b = blockIdx.z;
+    }
+    if constexpr (kMode == kFused) p.k = wv;  // gridDim.y is 1
+    p.d0 = kMode == kFused ? grp * kPlanes : (grp * kRowWaves + wv) * kPlanes;
+    p.nc = g.Dc - p.d0 < kPlanes ? g.Dc - p.d0 : kPlanes;
+    return p;
+}
+
+// LDS of the fused form: planes (rows of row_len elements) of the input in both
+// scan orders, then of the outputs of both.
+__host__ __device__ inline int row_len(int64_t L, int T) {
+    return static_cast<int>((L + T - 1) / T * T);
+}
+
+// The wave's sequences once more, position after position: lane 16 j + n has
+// state n of the j-th of four channels at a time. For waves whose joined runs
+// came out infinite or NaN: a product of factors above 1 over several runs may
+// leave the range of fp32 (0.2 a position over 512 is enough) where the states
+// themselves, zero or small, do not; the identity positions ahead of a reversed
+// plane form 0 A, NaN for an infinite A; and values that are not finite by
+// themselves are to be what the recurrence makes of them. About as slow as a
+// lane per channel, and never reached by states that decay. The kernel's
+// arguments are read again and nothing else of the wave's is used, so that the
+// scan holds no registers for it.
+template <int T, int kPlanes, typename Tin, typename Tout, int kMode, bool kZoh>
+__device__ __forceinline__ void walk_positions(char* lds) {
+    typedef const __attribute__((address_space(4))) RowArgs* Args;
+    Args args = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const RowArgs g = *(const RowArgs*)args;
+    const Place p = place_of<kMode, kPlanes>(g);
+    const int lane = threadIdx.x % kWave, n = lane % 16, N = g.N;
+    const int64_t L = g.L, bk = static_cast<int64_t>(p.b) * g.K + p.k;
+    const Tin* Bn = static_cast<const Tin*>(g.B) + (bk * N + (n < N ? n : 0)) * L;
+    const Tin* Cn = static_cast<const Tin*>(g.C) + (bk * N + (n < N ? n : 0)) * L;
+    const bool rev = p.k >= 2;
+    const int Lp = kMode == kFused ? row_len(L, T) : 0;
+    float* planes = reinterpret_cast<float*>(lds + 2 * kPlanes * Lp * sizeof(Tin)) +
+                    (p.k & 1) * kPlanes * Lp;
+#pragma unroll 1
+    for (int j0 = 0; j0 < p.nc; j0 += kWave / 16) {
+        const int ch = j0 + lane / 16;
+        const int d = p.d0 + (ch < p.nc ? ch : p.nc - 1), c = p.k * g.Dc + d;
+        const int64_t row = (bk * g.Dc + d) * L;
+        const Tin* drow = static_cast<const Tin*>(g.delta) + row;
+        const Tin* urow = static_cast<const Tin*>(g.u) +
+                          (kMode == kSeq ? row : (static_cast<int64_t>(p.b) * g.Dc + d) * L);
+        const float an = n < N ? g.A[static_cast<size_t>(c) * N + n] : 0.0f;
+        const float inv_a = kZoh ? 1.0f / an : 0.0f;
+        const float bias = g.dt_bias ? g.dt_bias[c] : 0.0f, dskip = g.D ? g.D[c] : 0.0f;
+        float h = 0.0f;
+#pragma unroll 1
+        for (int64_t t = 0; t < L; ++t) {
+            const float ut = to_f32(
+                urow[kMode == kSeq ? t : pixel_of(p.k, static_cast<int>(t), g.H, g.W)]);
+            const float dl = timescale(to_f32(drow[t]) + bias, g.softplus != 0);
+            const float x2 = dl * kLog2e * an, a = fast_exp2(x2), du = dl * ut;
+            const float q = kZoh ? zoh_q(x2, a, du, ut, inv_a) : du;
+            h = __builtin_fmaf(a, h, q * to_f32(Bn[t]));
+            float y = n < N ? to_f32(Cn[t]) * h : 0.0f;
+#pragma unroll
+            for (int m = 1; m < 16; m *= 2) y += __shfl_xor(y, m, kWave);
+            if (n != 0 || ch >= p.nc) continue;
+            y = __builtin_fmaf(dskip, ut, y);
+            if constexpr (kMode == kFused) {
+                // the reversed direction adds to its plane
+                float* o = planes + ch * Lp + (rev ? L - 1 - t : t);
+                *o = rev ? *o + y : y;
+            } else {
+                static_cast<Tout*>(g.y)[row + t] = from_f32<Tout>(y);
+            }
+        }
+    }
+}
+
 template <int S, int T, int CH, int NP, typename Tin, typename Tout, int kMode, bool kZoh, bool kN1>
 __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) void k_full_scan_rows(
     const RowArgs g) {
@@ -189,26 +286,10 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
     const int Dc = g.Dc, N = kN1 ? 1 : g.N;  // a multiple of NP
     const int64_t L = g.L;
 
-    // Workgroup i runs on XCD i % 8 (own L2): each XCD takes a contiguous
-    // range, so the channels that share B and C rows share an L2.
-    int grp, k, b;
-    if (g.n_wg) {
-        const unsigned bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-        const unsigned per = g.n_wg / 8, rem = g.n_wg % 8, xcd = bid % 8, slot = bid / 8;
-        unsigned id = xcd * per + (xcd < rem ? xcd : rem) + slot;
-        grp = static_cast<int>(id % static_cast<unsigned>(g.groups));
-        id /= static_cast<unsigned>(g.groups);
-        k = static_cast<int>(id % gridDim.y);
-        b = static_cast<int>(id / gridDim.y);
-    } else {
-        grp = blockIdx.x;
-        k = blockIdx.y;
-        b = blockIdx.z;
-    }
-    if constexpr (kMode == kFused) k = wv;  // gridDim.y is 1
-    const int d0 = kMode == kFused ? grp * kPlanes : (grp * kRowWaves + wv) * kPlanes;
+    const Place here = place_of<kMode, kPlanes>(g);
+    const int b = here.b, k = here.k, d0 = here.d0;
     if (kMode != kFused && d0 >= Dc) return;
-    const int nc = Dc - d0 < kPlanes ? Dc - d0 : kPlanes;  // channels of this wave
+    const int nc = here.nc;
     int slot_of[CH], cc[CH];  // this lane's channels; slots past nc repeat the last, unstored
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
@@ -220,7 +301,7 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
 
     // fused: LDS planes (rows of Lp elements): input in both scan orders,
     // then the outputs of both
-    const int Lp = kMode == kFused ? (iL + T - 1) / T * T : 0;
+    const int Lp = kMode == kFused ? row_len(iL, T) : 0;
     Tin* u_rows = reinterpret_cast<Tin*>(lds);
     Tin* u_cols = u_rows + kPlanes * Lp;
     float* y_planes = reinterpret_cast<float*>(u_cols + kPlanes * Lp);
@@ -332,6 +413,8 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
                        (static_cast<size_t>(b) * Dc + d0 + (ch < nc ? ch : 0)) * iL;
         Tin* pr = u_rows + ch * Lp;
         Tin* pc = u_cols + ch * Lp;
+        if (tid % kThr < Lp - iL)  // finite values past the last pixel
+            pr[iL + tid % kThr] = pc[iL + tid % kThr] = from_f32<Tin>(0.0f);
         for (int p = (tid % kThr) * kPer; p < iL; p += kThr * kPer) {
             Tin v[kPer];
             const int n = iL - p < kPer ? iL - p : kPer;
@@ -364,6 +447,7 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
     float carry[CH];  // lane n: state n leaving the previous chunk
 #pragma unroll
     for (int h = 0; h < CH; ++h) carry[h] = 0.0f;
+    int bad = 0;  // values that are not finite came up
     for (int64_t c0 = 0; c0 < L + lead; c0 += kChunk) {
         // 1. per-position products of the runs
         int at = 0;  // fused: the run's first element in its plane
@@ -489,6 +573,13 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
                 }
             }
         }
+        // A state that is not finite makes every output that it enters so,
+        // whatever C is, or else (the last run's) the carry.
+#pragma unroll
+        for (int h = 0; h < CH; ++h)
+            if (__builtin_amdgcn_ballot_w64(
+                    !(__builtin_isfinite(yv[h][0]) && __builtin_isfinite(carry[h]))) != 0)
+                bad = 1;
         // 4. outputs
         if constexpr (kMode == kFused) {
             // A plane takes the forward and the reversed direction of its
@@ -532,8 +623,24 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
         }
     }
 
-    if constexpr (kMode == kFused) {
+    if constexpr (kMode != kFused) {
+        if (bad) {
+            __threadfence();  // after the stores of the loop above
+            walk_positions<T, kPlanes, Tin, Tout, kMode, kZoh>(nullptr);
+        }
+    } else {
         __syncthreads();
+        // the input planes are no longer read: a word for each wave
+        uint32_t* redo = reinterpret_cast<uint32_t*>(lds);
+        if (lane == 0) redo[wv] = bad;
+        __syncthreads();
+        if (redo[0] | redo[1] | redo[2] | redo[3]) {
+#pragma unroll 1
+            for (int pass = 0; pass < 2; ++pass) {  // forward directions first
+                if (rev == (pass == 1)) walk_positions<T, kPlanes, Tin, Tout, kMode, kZoh>(lds);
+                __syncthreads();
+            }
+        }
         const int H = g.H, W = g.W;
         constexpr int kThr = kRowThreads / kPlanes;  // threads per plane, 4 pixels each
         const int ch = tid / kThr;
@@ -576,8 +683,6 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
 // 64 us, with 3072 rows 95 against 167 and N = 8 276 against 220).
 constexpr size_t kCuLds = 160 * 1024;
 inline size_t fused_lds_limit(int64_t N) { return N <= 2 ? kCuLds : kCuLds / 2; }
-
-inline int row_len(int64_t L, int T) { return static_cast<int>((L + T - 1) / T * T); }
 
 size_t fused_lds(int64_t L, int cpw, int T, size_t in_size) {
     return static_cast<size_t>(cpw) * row_len(L, T) * 2 * (in_size + sizeof(float));

@@ -3,6 +3,8 @@ bf16 length): run, segment and chunk boundaries, channel-slot tails, the fused
 2-D form (planes in LDS, reversed directions whose length is no multiple of a
 run), planes beyond LDS, both types and the zero-order-hold option, against the
 fp64 oracle at the tolerances of the other scans."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -128,3 +130,88 @@ def test_no_bias_no_skip_no_softplus():
     ref, scale = merged_oracle(inp, "full", **kw)
     assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
                  what="softplus off")
+
+
+def with_growth(inp, delta, live):
+    """inp with Delta = delta[t] as given (softplus and bias off), A in
+    [-1, -0.8] and positive u, B and C, where B is 0 but at the positions that
+    ``live`` marks (in each direction's own order)."""
+    pos = lambda a: (0.5 + np.abs(a) % 1.0).astype(np.float32)
+    N = inp.A.shape[1]
+    A = np.broadcast_to(np.linspace(-1.0, -0.8, N, dtype=np.float32), inp.A.shape)
+    f = {"delta": np.broadcast_to(delta, inp.delta.shape).astype(np.float32),
+         "B": pos(inp.B) * live.astype(np.float32), "C": pos(inp.C)}
+    f["x" if inp.u is None else "u"] = pos(inp.x if inp.u is None else inp.u)
+    bits = dict(inp.bits or {})
+    if inp.shape.dtype == "bf16":
+        for name in f:
+            f[name], bits[name] = workloads.bf16_round(f[name])
+    return dataclasses.replace(inp, A=np.ascontiguousarray(A), bits=bits, **f)
+
+
+def check_growth(inp, layout, rtol, options=0):
+    kw = dict(softplus=False, use_bias=False, use_d=False)
+    got = to_f64(run_scan(inp, "full", layout, out_dtype=torch.float32, **kw,
+                          options=vmb.VMB_SCAN_ZOH if options else None))
+    if layout == "seq":
+        ref, scale = oracle_seq(inp, "full", "seq", options=options, **kw), None
+    else:
+        ref, scale = merged_oracle(inp, "full", options=options, **kw)
+    assert_close(got, ref, rtol=rtol, atol=1e-5, scale=scale, what="growing states")
+
+
+# Factors above 1 whose product over the sequence (or a chunk of it) is beyond
+# fp32, on a state that is 0 until the last positions: finite, step by step.
+# Each step rounds by at most 3 * 2^-24 (exponent, exp2, fma), 160 of them at most.
+@pytest.mark.parametrize("layout,b,H,W,c,N,dtype,step", [
+    ("seq", 1, 1, 49, 7, 1, "f32", 3.0), ("seq", 1, 1, 120, 9, 2, "bf16", 1.5),
+    ("seq", 1, 1, 250, 5, 4, "f32", 1.0), ("seq", 1, 1, 1030, 5, 4, "f32", 0.25),
+    ("seq", 1, 1, 700, 300, 16, "bf16", 0.25), ("2d", 1, 7, 9, 5, 2, "f32", 3.0),
+    ("2d", 1, 23, 29, 3, 8, "f32", 0.25), ("2d", 1, 90, 93, 2, 8, "bf16", 0.25)])
+def test_growing_states(layout, b, H, W, c, N, dtype, step):
+    log(f"rows growing {layout} {H}x{W} N={N} {dtype}")
+    inp = inputs(b, H, W, c, N, layout, dtype)
+    L = H * W
+    live = np.arange(L) >= L - int(40 / step)
+    inp = with_growth(inp, np.full(L, -step, np.float32), live)
+    for options in (0, oracle.ZOH) if N < 16 else (0,):  # N = 16 with ZOH: other kernels
+        check_growth(inp, layout, 160 * 3 * 2.0 ** -24, options)
+
+
+# a state that decays to 1e-28 before a chunk whose product of factors is 1e55
+def test_growing_small_state():
+    log("rows growing small state")
+    inp = inputs(1, 1, 1030, 5, 1, "seq")
+    delta = np.zeros(1030, np.float32)
+    delta[455:460], delta[460:510], delta[520:571] = 1.0, 1.3, -2.5
+    check_growth(with_growth(inp, delta, np.arange(1030) < 460), "seq", 110 * 3 * 2.0 ** -24 + 1e-5)
+
+
+# A = -inf forgets the state at every position; a plane whose length is no
+# multiple of a run has identity positions ahead of its reversed directions
+@pytest.mark.parametrize("layout,H,W", [("2d", 7, 9), ("2d", 11, 11), ("2d", 23, 29), ("seq", 1, 513)])
+def test_infinite_decay(layout, H, W):
+    log(f"rows A = -inf {layout} {H}x{W}")
+    inp = inputs(1, H, W, 5, 2, layout)
+    inp.A[:, 0] = -np.inf
+    got = to_f64(run_scan(inp, "full", layout))
+    if layout == "seq":
+        ref, scale = oracle_seq(inp, "full", layout), None
+    else:
+        ref, scale = merged_oracle(inp, "full")
+    assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                 what="A = -inf")
+
+
+# an infinite input: before it, and in the other channels, nothing changes
+@pytest.mark.parametrize("L", [49, 200, 1030])
+def test_infinite_input(L):
+    log(f"rows u = inf L={L}")
+    inp = inputs(1, 1, L, 6, 2, "seq")
+    at = L * 2 // 3
+    inp.u[0, 1, 3, at] = np.inf
+    got, ref = to_f64(run_scan(inp, "full", "seq")), oracle_seq(inp, "full", "seq")
+    bad = ~np.isfinite(ref)
+    assert bad[0, 1, 3, at:].all() and bad.sum() == L - at
+    assert not np.isfinite(got[bad]).any()
+    assert_close(np.where(bad, 0.0, got), np.where(bad, 0.0, ref), **FP32_TOL, what="u = inf")
