@@ -299,25 +299,10 @@ __device__ __forceinline__ void pair_phase2(const float (&a0)[T], const float (&
 // [cs, cs + len) of the row, len <= kStageMax. The copy goes straight from
 // global memory to LDS (gfx950 global_load_lds: each lane of a wave moves 16
 // or 4 bytes to LDS at base + lane * size), no registers involved. Rows of
-// whole 16-byte pieces move 16-byte pieces, others 4-byte words: one fp32 or
-// two bf16 elements. bf16 rows of odd length start on a word or in the middle
-// of one by turns (N L elements a direction, N even: state n's row starts n L
-// elements from a word); the latter are copied from the word their first
-// element lies in, one element early, and read one element further on
-// (row_shift). A copy may take one element past its row: the next row's, and
-// none past the tensor, whose rows together are whole words. The issuing wave
-// must wait for vmcnt before the barrier that publishes them.
+// whole 16-byte pieces move 16-byte pieces, others 4-byte words (one fp32 or
+// two bf16 elements: bf16 rows reach this kernel with even lengths only). The
+// issuing wave must wait for vmcnt before the barrier that publishes them.
 constexpr int kStageMax = 4 * kWave * 13;
-// LDS row of one state: room for the shifted copy (bf16), 16-byte aligned
-template <typename Tin>
-constexpr int stage_row_size() {
-    return kStageMax + (sizeof(Tin) == 2 ? 8 : 0);
-}
-// how far into its copy the row of state s of a pair starts
-template <typename Tin>
-__device__ __forceinline__ int row_shift(int s, int L) {
-    return sizeof(Tin) == 2 ? (s & L & 1) : 0;
-}
 constexpr int kComputeWaves = 12;  // G channels x Wv waves
 constexpr int kCopyWaves = 4;      // one per SIMD, copies only
 constexpr int kStageThreads = (kComputeWaves + kCopyWaves) * kWave;
@@ -330,7 +315,7 @@ __device__ __forceinline__ void stage_pieces(const Tin* src, Tin* dst, int len, 
                                              int lane) {
     constexpr int kPer = kBytes / static_cast<int>(sizeof(Tin));  // elements per lane-piece
     constexpr int kSpan = kWave * kPer;                            // per wave-instruction
-    constexpr int kIt = (stage_row_size<Tin>() + kCopyWaves * kSpan - 1) / (kCopyWaves * kSpan);
+    constexpr int kIt = (kStageMax + kCopyWaves * kSpan - 1) / (kCopyWaves * kSpan);
     const int jl = lane * kPer;
 #pragma unroll
     for (int it = 0; it < kIt; ++it) {
@@ -364,8 +349,8 @@ __device__ __forceinline__ void wave_copy(const Tin* src, Tin* dst, int len, int
 // Slot idx of size elements in the two C stage buffers viewed end to end
 // (slots never straddle the two arrays).
 template <typename Tin>
-__device__ __forceinline__ Tin* stage_slot(Tin (*a)[stage_row_size<Tin>()],
-                                           Tin (*b)[stage_row_size<Tin>()], int idx, int size) {
+__device__ __forceinline__ Tin* stage_slot(Tin (*a)[kStageMax], Tin (*b)[kStageMax], int idx,
+                                           int size) {
     const int per = (2 * kStageMax) / size;
     return idx < per ? &a[0][0] + idx * size : &b[0][0] + (idx - per) * size;
 }
@@ -387,8 +372,7 @@ __device__ __forceinline__ void stage_one(const Tin* base, int p, int s, Tin* ds
     const int ci = p / kPairs, n0 = 2 * (p - ci * kPairs);
     const int cs = ci * chunk;
     const int len = L - cs < chunk ? L - cs : chunk;
-    const int sh = row_shift<Tin>(s, L);
-    stage_row(base + static_cast<size_t>(n0 + s) * L - sh, dst, cs, len + sh, vec4, issuer, lane);
+    stage_row(base + static_cast<size_t>(n0 + s) * L, dst, cs, len, vec4, issuer, lane);
 }
 
 // Wait until this wave's outstanding vector-memory operations (including the
@@ -417,9 +401,8 @@ __global__ __launch_bounds__(kStageThreads) void k_full_scan_chunked(
     __shared__ float hcar[kComputeWaves][N];    // per wave: state carried into the next chunk
     // B and C slices of a pair of states, double-buffered (distinct arrays so
     // that copies into one buffer never order reads of the other)
-    constexpr int kRow = stage_row_size<Tin>();
-    __shared__ __align__(16) Tin bst0[2][kRow], bst1[2][kRow];
-    __shared__ __align__(16) Tin cst0[2][kRow], cst1[2][kRow];
+    __shared__ __align__(16) Tin bst0[2][kStageMax], bst1[2][kStageMax];
+    __shared__ __align__(16) Tin cst0[2][kStageMax], cst1[2][kStageMax];
     // per compute wave: its outputs on their way to a coalesced store
     __shared__ __align__(16) float ystage[kComputeWaves][kWave * T];
 
@@ -477,8 +460,8 @@ __global__ __launch_bounds__(kStageThreads) void k_full_scan_chunked(
         if (kTwoD && staged) __syncthreads();  // pairs with the plane barrier
         __syncthreads();
         for (int p = 0; p < npairs; ++p) {
-            Tin (*cdst)[kRow] = (p & 1) ? cst1 : cst0;
-            Tin (*bdst)[kRow] = (p & 1) ? bst0 : bst1;
+            Tin (*cdst)[kStageMax] = (p & 1) ? cst1 : cst0;
+            Tin (*bdst)[kStageMax] = (p & 1) ? bst0 : bst1;
             stage(Cb, p, 0, cdst[0]);
             stage(Cb, p, 1, cdst[1]);
             if (p + 1 < npairs) {
@@ -516,7 +499,6 @@ __global__ __launch_bounds__(kStageThreads) void k_full_scan_chunked(
         }
     }
     const int run = (w * kWave + lane) * T;  // this lane's first position inside a chunk
-    const int sh1 = row_shift<Tin>(1, L);
 
     // This lane's run of delta and u for chunk ci; chunk 0's loads are issued
     // before the first barrier so that they overlap the first B copy.
@@ -577,19 +559,19 @@ __global__ __launch_bounds__(kStageThreads) void k_full_scan_chunked(
         // One pair step per barrier: phase 1 reads B of the pair (published
         // by the previous barrier), the barrier publishes the wave aggregates
         // and C of the pair, phase 2 reads them.
-        auto pair_step = [&](int n0, Tin (*bcur)[kRow], Tin (*ccur)[kRow],
+        auto pair_step = [&](int n0, Tin (*bcur)[kStageMax], Tin (*ccur)[kStageMax],
                              float (*xq)[G][kSlots][2]) {
             constexpr bool kOut = !kOne;  // chunks pass a carry on
             const float2 a01 = *reinterpret_cast<const float2*>(an + n0);
             const float inv0 = kZoh ? 1.0f / a01.x : 0.0f, inv1 = kZoh ? 1.0f / a01.y : 0.0f;
             float a0[T], bu0[T], a1[T], bu1[T];
             float Pin0, Hin0, Pin1, Hin1;
-            pair_phase1<T, Tin, kZoh>(a01.x, a01.y, dl2, du, s2, &bcur[0][run], &bcur[1][run + sh1], a0,
+            pair_phase1<T, Tin, kZoh>(a01.x, a01.y, dl2, du, s2, &bcur[0][run], &bcur[1][run], a0,
                                       bu0, a1, bu1, Pin0, Hin0, Pin1, Hin1, xq[0][g], xq[1][g],
                                       lane, kLead + w, uv, inv0, inv1);
             __syncthreads();
             pair_phase2<T, kWv, kOut>(a0, bu0, a1, bu1, Pin0, Hin0, Pin1, Hin1, &ccur[0][run],
-                                      &ccur[1][run + sh1], yv, xq[0][g], xq[1][g], &hcar[wv][n0],
+                                      &ccur[1][run], yv, xq[0][g], xq[1][g], &hcar[wv][n0],
                                       &hcar[wv][n0 + 1], lane, w);
         };
 #pragma unroll 1

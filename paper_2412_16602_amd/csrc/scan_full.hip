@@ -10,7 +10,12 @@
 
 namespace vmb {
 
-bool use_chunked_full(const ScanArgs& a) { return a.N == 16 && a.L > kShortMaxL; }
+// The chunked kernel copies B and C rows into LDS in pieces of 4 or 16
+// bytes; a bf16 row of odd length has neither its start nor its end on a
+// 4-byte boundary.
+bool use_chunked_full(const ScanArgs& a) {
+    return a.N == 16 && a.L > kShortMaxL && !(a.in_dt == VMB_BF16 && (a.L & 1));
+}
 
 // bf16, N = 16: with enough rows to fill the chip but too few for the tile
 // kernel's 64-channel workgroups to, one wave per sequence is the fastest, since
@@ -22,13 +27,14 @@ bool use_chunked_full(const ScanArgs& a) { return a.N == 16 && a.L > kShortMaxL;
 // 56x56: 3072 rows 86 / 91, 12288 316 / 338: chunked.)
 bool use_rows_full(const ScanArgs& a) {
     const int64_t rows = a.batch * a.K * a.channels;
-    return a.N == 16 && a.in_dt == VMB_BF16 && a.L > 64 && rows >= 1200 && rows < 49152 &&
-           a.batch <= 65535 && a.K <= 65535;
+    return a.N == 16 && a.in_dt == VMB_BF16 && a.L > 64 && rows >= 1200 &&
+           rows < 49152 && a.batch <= 65535 && a.K <= 65535;
 }
 
 vmb_status launch_full_scan(const ScanArgs& a) {
-    // the zero-order-hold B runs in the tile, positions-over-lanes and lane
-    // kernels (not the short-sequence one: those shapes take the tile kernel)
+    // the zero-order-hold B runs in the tile, positions-over-lanes and
+    // one-wave-per-sequence kernels (not the short-sequence one: those shapes
+    // take the tile kernel)
     const bool zoh = (a.options & VMB_SCAN_ZOH) != 0;
     if (!zoh && use_rows_full(a)) return launch_full_rows(a);
     const bool tiles =

@@ -41,7 +41,7 @@ def test_channel_group_tails(channels):
 
 
 # bf16 rows of 16-byte pieces (L % 8 == 0), of 4-byte pieces (L even) and of
-# odd length (not on 4-byte boundaries: the lane-per-channel kernel takes them)
+# odd length (not on 4-byte boundaries: the one-wave-per-sequence kernel takes them)
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 @pytest.mark.parametrize("H,W", [(32, 64), (33, 62), (33, 61)])
 def test_bf16(out, H, W):
