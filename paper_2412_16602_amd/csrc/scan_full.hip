@@ -24,11 +24,17 @@ bool use_chunked_full(const ScanArgs& a) {
 // 56x56, 192 channels: 768 rows 40 / 60, 1536 73 / 70, 6144 273 / 150, 24576
 // 765 / 531, 36864 928 / 785, 49152 1008 / 1039; 28x28: 1536 rows 40 / 22, 24576
 // 218 / 170; 14x14: 3072 rows 29 / 16; 7x7 (L = 49): 6144 rows 22 / 23. (fp32,
-// 56x56: 3072 rows 86 / 91, 12288 316 / 338: chunked.)
+// 56x56: 3072 rows 86 / 91, 12288 316 / 338: chunked.) Planes beyond 6144
+// positions, for which the workspace has no column-major copies and both
+// gather directions 1 and 3: 96x96, 24576 rows 3094 / 1526; 97x101, 17600 rows
+// 11800 / 1424; 128x64, 16384 rows 2040 / 945.
+// Rows that the tile kernel does not take (odd lengths) have no upper limit
+// (short kernel: 15x15, 98304 rows 333 / 149; 7x13, 196608 rows 324 / 158), and
+// above kShortMaxL none of the others takes them at all.
 bool use_rows_full(const ScanArgs& a) {
     const int64_t rows = a.batch * a.K * a.channels;
     return a.N == 16 && a.in_dt == VMB_BF16 && a.L > 64 && rows >= 1200 &&
-           rows < 49152 && a.batch <= 65535 && a.K <= 65535;
+           (rows < 49152 || !tiles_take(a)) && a.batch <= 65535 && a.K <= 65535;
 }
 
 vmb_status launch_full_scan(const ScanArgs& a) {

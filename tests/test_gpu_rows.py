@@ -105,6 +105,25 @@ def test_two_channels_a_lane(layout, b, H, W, c, N, dtype):
                      what=f"2d {H}x{W} c={c}")
 
 
+# N = 16 in bf16: from 1200 rows on in place of the short and chunked kernels
+# (1196, 1200), up to 49152 where the tile kernel takes the length (49148, 49152;
+# an odd one stays), L = 64 and 65
+@pytest.mark.parametrize("b,c,H,W,layout", [
+    (13, 23, 6, 12, "seq"), (12, 25, 6, 12, "2d"), (1, 299, 21, 20, "2d"), (1, 300, 21, 20, "seq"),
+    (11, 1117, 6, 11, "2d"), (12, 1024, 6, 11, "2d"), (12, 1024, 5, 15, "2d"),
+    (12, 1024, 1, 65, "seq"), (5, 61, 8, 8, "2d"), (5, 61, 5, 13, "2d")])
+def test_row_limits_n16(layout, b, c, H, W):
+    log(f"rows limits {layout} b={b} {H}x{W} c={c}")
+    inp = inputs(b, H, W, c, 16, layout, "bf16", d_value=1.0)
+    got = to_f64(run_scan(inp, "full", layout, out_dtype=torch.float32))
+    if layout == "seq":
+        assert_close(got, oracle_seq(inp, "full", "seq"), **FP32_TOL, what=f"{H}x{W} c={c}")
+    else:
+        ref, scale = merged_oracle(inp, "full")
+        assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                     what=f"2d {H}x{W} c={c}")
+
+
 @pytest.mark.parametrize("N", [1, 8])
 @pytest.mark.parametrize("layout,H,W", [("seq", 1, 530), ("2d", 6, 7), ("2d", 23, 25),
                                         ("2d", 90, 91)])
