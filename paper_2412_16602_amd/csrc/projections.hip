@@ -99,7 +99,10 @@ struct Step {
     float w[MB][kCh];
 };
 
-template <typename T, int MB, int VP, int KS>
+// kFlat: sequences shorter than a vector. Positions run on over the batch,
+// column c of block j is position 16 j + c of the wave's, each loaded and
+// stored by itself (groups is then the number of positions).
+template <typename T, int MB, int VP, int KS, bool kFlat>
 __global__ __launch_bounds__(kThreads, 2) void k_projections(
     const T* __restrict__ u, const float* __restrict__ W, const float* __restrict__ Wdt,
     T* __restrict__ delta, T* __restrict__ Bo, T* __restrict__ Co, int K, int Dc, int L, int N,
@@ -125,29 +128,66 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
     const int M = R + 2 * N;  // (M + 15) / 16 == MB
     const size_t l = static_cast<size_t>(L);
 
-    // this lane's group of VP positions
-    const int per_seq = (L + VP - 1) / VP;
-    const int64_t gi = static_cast<int64_t>(tile) * 16 + col;
-    const bool ok = gi < groups;
-    const int64_t gc = ok ? gi : groups - 1;
-    const int64_t b = gc / per_seq;
-    const int tg = static_cast<int>(gc - b * per_seq) * VP;
-    const int t0 = tg + VP <= L ? tg : L - VP;
-    const size_t bk = static_cast<size_t>(b) * K + k;
+    // this lane's VP positions: of one sequence, from tj[0] on, or (kFlat) the
+    // position tj[j] of (batch, direction) bkj[j] each
+    constexpr int kSeqs = kFlat ? VP : 1;
+    size_t bkj[kSeqs];
+    int tj[kSeqs];
+    size_t at0[kSeqs];  // in channel 0 of u and delta
+    bool okj[kSeqs];
+    if constexpr (kFlat) {
+#pragma unroll
+        for (int j = 0; j < VP; ++j) {
+            const int64_t p = static_cast<int64_t>(tile) * (16 * VP) + 16 * j + col;
+            okj[j] = p < groups;
+            const int64_t pc = okj[j] ? p : groups - 1;
+            const int64_t b = pc / L;
+            tj[j] = static_cast<int>(pc - b * L);
+            bkj[j] = static_cast<size_t>(b) * K + k;
+        }
+    } else {
+        const int per_seq = (L + VP - 1) / VP;
+        const int64_t gi = static_cast<int64_t>(tile) * 16 + col;
+        okj[0] = gi < groups;
+        const int64_t gc = okj[0] ? gi : groups - 1;
+        const int64_t b = gc / per_seq;
+        const int tg = static_cast<int>(gc - b * per_seq) * VP;
+        tj[0] = tg + VP <= L ? tg : L - VP;
+        bkj[0] = static_cast<size_t>(b) * K + k;
+    }
+#pragma unroll
+    for (int j = 0; j < kSeqs; ++j) at0[j] = bkj[j] * Dc * l + tj[j];
+    const bool ok = okj[0];  // the first of them: none where not
+    // the positions off elements on from at0 in u, and from at in out
+    auto load_at = [&](Vec<T, VP>& v, size_t off) {
+        if constexpr (kFlat) {
+#pragma unroll
+            for (int j = 0; j < VP; ++j) v.v[j] = u[at0[j] + off];
+        } else {
+            __builtin_memcpy(&v, u + at0[0] + off, sizeof(v));
+        }
+    };
+    auto store_at = [&](T* out, const size_t (&at)[kSeqs], size_t off, const Vec<T, VP>& v) {
+        if constexpr (kFlat) {
+#pragma unroll
+            for (int j = 0; j < VP; ++j)
+                if (okj[j]) out[at[j] + off] = v.v[j];
+        } else {
+            __builtin_memcpy(out + at[0] + off, &v, sizeof(v));
+        }
+    };
 
     // 1. x_dbl
-    const T* up = u + (bk * Dc) * l + t0;  // channel 0
     const float* Wk = W + static_cast<size_t>(k) * M * Dc;
     // W row of this lane in each row block (the last block's rows past M repeat one)
     const int m_last = 16 * (MB - 1) + col;
     const float* wlane = Wk + static_cast<size_t>(col) * Dc + kq * kCh;
     const float* wlast = Wk + static_cast<size_t>(m_last < M ? m_last : M - 1) * Dc + kq * kCh;
-    const T* ulane = up + static_cast<size_t>(kq * kCh) * l;
     auto load = [&](Step<T, MB, VP>& s, int g) {  // a whole step, no branches
         const size_t c0 = static_cast<size_t>(g) * kStep;
-        const T* p = ulane + c0 * l;
+        const size_t first = (c0 + kq * kCh) * l;
 #pragma unroll
-        for (int i = 0; i < kCh; ++i) __builtin_memcpy(&s.u[i], p + i * l, sizeof(s.u[i]));
+        for (int i = 0; i < kCh; ++i) load_at(s.u[i], first + i * l);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
             __builtin_memcpy(s.w[mb],
@@ -160,7 +200,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
 #pragma unroll
         for (int i = 0; i < kCh; ++i) {
             const int c = c0 + i < Dc ? c0 + i : Dc - 1;
-            __builtin_memcpy(&s.u[i], up + static_cast<size_t>(c) * l, sizeof(s.u[i]));
+            load_at(s.u[i], static_cast<size_t>(c) * l);
 #pragma unroll
             for (int j = 0; j < VP; ++j)
                 if (c0 + i >= Dc) s.u[i].v[j] = from_f32<T>(0.0f);
@@ -298,14 +338,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
 #pragma unroll
                 for (int j = 0; j < VP; ++j) o.v[j] = from_f32<T>(acc[mb][j][v]);
                 const int n = m - R;
-                T* dst = n < N ? Bo + (bk * N + n) * l : Co + (bk * N + n - N) * l;
-                __builtin_memcpy(dst + t0, &o, sizeof(o));
+                size_t at[kSeqs];
+#pragma unroll
+                for (int j = 0; j < kSeqs; ++j) at[j] = bkj[j] * N * l + tj[j];
+                store_at(n < N ? Bo : Co, at, (n < N ? n : n - N) * l, o);
             }
         }
     }
 
     // 2. delta
-    T* dp = delta + (bk * Dc) * l + t0;
     if (Wdt == nullptr) {
         // R = 1, Broadcast_D: every channel takes x_dbl row 0 (register 0 of
         // lane group 0); the lane groups share the channels
@@ -314,7 +355,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
         for (int j = 0; j < VP; ++j) o.v[j] = from_f32<T>(__shfl(acc[0][j][0], col, 64));
         if (!ok) return;
         for (int d = 4 * ks + kq; d < Dc; d += 4 * KS)
-            __builtin_memcpy(dp + static_cast<size_t>(d) * l, &o, sizeof(o));
+            store_at(delta, at0, static_cast<size_t>(d) * l, o);
         return;
     }
     constexpr int RB = MB < kMaxR / 16 ? MB : kMaxR / 16;  // blocks that may hold timescale rows
@@ -368,7 +409,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
                 Vec<T, VP> s;
 #pragma unroll
                 for (int j = 0; j < VP; ++j) s.v[j] = from_f32<T>(o[j][v]);
-                if (d < Dc) __builtin_memcpy(dp + static_cast<size_t>(d) * l, &s, sizeof(s));
+                if (d < Dc) store_at(delta, at0, static_cast<size_t>(d) * l, s);
             }
         };
         const int blocks = (Dc + 15) / 16;
@@ -411,27 +452,28 @@ struct Args {
     hipStream_t s;
 };
 
-template <typename T, int MB, int VP, int KS>
+template <typename T, int MB, int VP, int KS, bool kFlat>
 void launch_mb(const Args& a) {
-    const int64_t groups = a.batch * ((a.L + VP - 1) / VP);
+    const int64_t l = a.L, groups = kFlat ? (a.batch * l + VP - 1) / VP : a.batch * ((l + VP - 1) / VP);
     const int64_t tiles = (groups + 15) / 16;
     constexpr int PW = kWaves / KS;
     const int64_t wgs = (tiles + PW - 1) / PW * a.K;
-    hipLaunchKernelGGL((k_projections<T, MB, VP, KS>), dim3(static_cast<unsigned>(wgs)),
+    hipLaunchKernelGGL((k_projections<T, MB, VP, KS, kFlat>), dim3(static_cast<unsigned>(wgs)),
                        dim3(kThreads), 0, a.s, static_cast<const T*>(a.u), a.W, a.W_dt,
                        static_cast<T*>(a.delta), static_cast<T*>(a.B), static_cast<T*>(a.C), a.K,
-                       a.Dc, a.L, a.N, a.R, groups, static_cast<int>(tiles));
+                       a.Dc, a.L, a.N, a.R, kFlat ? a.batch * l : groups,
+                       static_cast<int>(tiles));
 }
 
-template <typename T, int VP, int KS>
+template <typename T, int VP, int KS, bool kFlat = false>
 void launch_vp(const Args& a) {
     switch ((a.R + 2 * a.N + 15) / 16) {
-        case 1: return launch_mb<T, 1, VP, KS>(a);
-        case 2: return launch_mb<T, 2, VP, KS>(a);
-        case 3: return launch_mb<T, 3, VP, KS>(a);
-        case 4: return launch_mb<T, 4, VP, KS>(a);
-        case 5: return launch_mb<T, 5, VP, KS>(a);
-        default: return launch_mb<T, 6, VP, KS>(a);
+        case 1: return launch_mb<T, 1, VP, KS, kFlat>(a);
+        case 2: return launch_mb<T, 2, VP, KS, kFlat>(a);
+        case 3: return launch_mb<T, 3, VP, KS, kFlat>(a);
+        case 4: return launch_mb<T, 4, VP, KS, kFlat>(a);
+        case 5: return launch_mb<T, 5, VP, KS, kFlat>(a);
+        default: return launch_mb<T, 6, VP, KS, kFlat>(a);
     }
 }
 
@@ -444,12 +486,23 @@ void launch_vp(const Args& a) {
 //   2 x 128x512 fp32 rank 6  8192 tiles   217  210  215  252
 // so four waves share a tile until the tiles alone fill the chip several
 // times over (then two: less to exchange), and tiles get narrower only when
-// there are fewer than compute units. Sequences shorter than a vector take
-// single positions.
+// there are fewer than compute units. Sequences shorter than a vector
+// (L < 4): single positions a lane while there are fewer tiles of 64 than
+// compute units; from there on tiles over the batch, since single positions
+// read W four times as often. Measured (us; single positions, four waves, two):
+//   16384 x 3, 192 channels, rank 6    fp32 188 161 163   bf16 211 162 143
+//   65536 x 3, 64 channels, N = 8             234 214 242        200 201 178
+//   65536 x 1, 96 channels, rank 3            158 136 120        135 113 125
+//   4096 x 3, 64 channels, rank 2              20  19  24         19  18  20
 template <typename T>
 void launch_t(const Args& a) {
-    const int64_t tiles4 = (a.batch * ((a.L + 3) / 4) + 15) / 16 * a.K;
-    if (a.L < 4) return launch_vp<T, 1, 4>(a);
+    if (a.L < 4) {
+        const int64_t tiles = (a.batch * a.L + 63) / 64 * a.K;
+        if (tiles < 256) return launch_vp<T, 1, 4>(a);
+        if (sizeof(T) == 2 && a.L > 1 && tiles >= 2048) return launch_vp<T, 4, 2, true>(a);
+        return launch_vp<T, 4, 4, true>(a);
+    }
+    const int64_t tiles4 = (a.batch * ((a.L + int64_t{3}) / 4) + 15) / 16 * a.K;
     if (tiles4 < 256) return launch_vp<T, 2, 4>(a);
     if (tiles4 >= 4096) return launch_vp<T, 4, 2>(a);
     launch_vp<T, 4, 4>(a);

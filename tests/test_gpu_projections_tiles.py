@@ -21,6 +21,9 @@ CASES = [  # batch, K, Dc, L, N, R
     (2, 4, 48, 1027, 16, 17),   # four positions a lane, four waves: a partial group
     (4, 4, 17, 1025, 4, 33),
     (1, 1, 70, 16390, 16, 4),
+    (4097, 4, 17, 1, 8, 5),     # positions over the batch: a partial tile
+    (1403, 4, 33, 3, 16, 3),
+    (11001, 4, 20, 3, 4, 2),    # the same, two waves a tile in bf16
     (8, 4, 20, 8195, 16, 5),    # two waves a tile, more waves than steps
     (8, 4, 100, 8197, 1, 18),
 ]
