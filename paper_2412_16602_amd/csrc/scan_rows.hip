@@ -170,6 +170,7 @@ struct RowArgs {
     int batch, K, Dc, N, H, W, softplus;
     int64_t L;
     int groups;     // workgroups per (batch, direction), or per batch when fused
+    int first;      // the first of them (in a launch over part of the channels)
     unsigned n_wg;  // whole grid, 0 when it is not renumbered
 };
 
@@ -197,6 +198,7 @@ __device__ __forceinline__ Place place_of(const RowArgs& g) {
         p.k = blockIdx.y;
         p.b = blockIdx.z;
     }
+    grp += g.first;
     if constexpr (kMode == kFused) p.k = wv;  // gridDim.y is 1
     p.d0 = kMode == kFused ? grp * kPlanes : (grp * kRowWaves + wv) * kPlanes;
     p.nc = g.Dc - p.d0 < kPlanes ? g.Dc - p.d0 : kPlanes;
@@ -695,15 +697,21 @@ vmb_status launch_rows(const ScanArgs& a, void* y, const void* xt) {
     const int64_t groups = (a.channels + per - 1) / per;
     if (groups > 0x7fffffffLL) return VMB_ERR_UNSUPPORTED;
     const int64_t gy = kMode == kFused ? 1 : a.K;
-    const int64_t n_wg = groups * gy * a.batch;
-    RowArgs g{a.u, a.delta, a.A, a.B, a.C, a.D, a.dt_bias, y, xt,
-              int(a.batch), int(a.K), int(a.channels), int(a.N), int(a.H), int(a.W), a.softplus,
-              a.L, int(groups), n_wg <= 0x7fffffffLL ? static_cast<unsigned>(n_wg) : 0u};
     const size_t lds = kMode == kFused ? fused_lds(a.L, kPlanes, T, sizeof(Tin)) : 0;
-    const dim3 grid(static_cast<unsigned>(groups), static_cast<unsigned>(gy),
-                    static_cast<unsigned>(a.batch));
-    hipLaunchKernelGGL((k_full_scan_rows<S, T, CH, NP, Tin, Tout, kMode, kZoh, kN1>), grid,
-                       dim3(kRowThreads), lds, a.stream, g);
+    // a grid has fewer than 2^32 threads in x
+    constexpr int64_t kMost = (int64_t{1} << 32) / kRowThreads - 1;
+    for (int64_t first = 0; first < groups; first += kMost) {
+        const int64_t part = groups - first < kMost ? groups - first : kMost;
+        const int64_t n_wg = part * gy * a.batch;
+        const RowArgs g{a.u, a.delta, a.A, a.B, a.C, a.D, a.dt_bias, y, xt,
+                        int(a.batch), int(a.K), int(a.channels), int(a.N), int(a.H), int(a.W),
+                        a.softplus, a.L, int(part), int(first),
+                        n_wg <= 0x7fffffffLL ? static_cast<unsigned>(n_wg) : 0u};
+        const dim3 grid(static_cast<unsigned>(part), static_cast<unsigned>(gy),
+                        static_cast<unsigned>(a.batch));
+        hipLaunchKernelGGL((k_full_scan_rows<S, T, CH, NP, Tin, Tout, kMode, kZoh, kN1>), grid,
+                           dim3(kRowThreads), lds, a.stream, g);
+    }
     return check_launch();
 }
 

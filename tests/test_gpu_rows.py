@@ -11,7 +11,7 @@ import torch
 
 import oracle
 import workloads
-from gpu_util import BF16_TOL, FP32_TOL, assert_close, log, oracle_seq, run_scan, to_f64
+from gpu_util import BF16_TOL, FP32_TOL, assert_close, dev, log, oracle_seq, run_scan, to_f64
 from paper_2412_16602_amd import vmb
 from test_gpu_scan import merged_oracle
 
@@ -236,3 +236,32 @@ def test_infinite_input(L):
     assert bad[0, 1, 3, at:].all() and bad.sum() == L - at
     assert not np.isfinite(got[bad]).any()
     assert_close(np.where(bad, 0.0, got), np.where(bad, 0.0, ref), **FP32_TOL, what="u = inf")
+
+
+# more channels than one launch takes (2^28 with one wave for 16, 2^26 with one
+# workgroup for 4): the outputs repeat those of a few channels, bit for bit
+@pytest.mark.parametrize("layout,channels", [("seq", 2 ** 28 + 5), ("2d", 2 ** 26 + 3)])
+def test_many_channels(layout, channels):
+    log(f"rows {layout} channels={channels}")
+    two_d, K, few = layout == "2d", 4 if layout == "2d" else 1, 997
+    g = torch.Generator().manual_seed(1)
+    period = lambda n: torch.rand(n, generator=g).add_(0.5).to(torch.bfloat16).to(dev())
+    u1, d1 = period(few), period(few)
+    B = torch.ones((1, K, 1, 1), dtype=torch.bfloat16, device=dev())
+
+    def call(c):
+        rep = lambda p: p.repeat(-(-c // few))[:c]
+        u = rep(u1).view(1, 1, c, 1)
+        delta = rep(d1).view(1, 1, c, 1).expand(1, K, c, 1).contiguous()
+        A = torch.full((K * c, 1), -1.0, device=dev())
+        y = torch.empty_like(u)
+        lay = vmb.VMB_LAYOUT_2D if two_d else vmb.VMB_LAYOUT_SEQ
+        if two_d:
+            u, y = u.view(1, c, 1, 1), y.view(1, c, 1, 1)
+        vmb.vmb_selective_scan_fwd_ex(u, delta, A, B, B, None, None, False, y, vmb.VMB_SCAN_ZOH,
+                                      layout=lay)
+        return y.view(-1)
+
+    want = call(few).repeat(-(-channels // few))[:channels]
+    assert torch.isfinite(want[:few].float()).all()
+    assert torch.equal(call(channels), want)
