@@ -40,3 +40,24 @@ def test_vectors(batch, channels, P, gate, affine, dtype):
     torch.cuda.synchronize()
     ref = oracle.out_norm_gate(y, z, gamma, beta, 1e-5)
     assert_close(to_f64(out), ref, **(FP32_TOL if dtype == "f32" else BF16_TOL), what="norm")
+
+
+# pointers on an element, not on a vector
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_unaligned(dtype):
+    log(f"norm vec unaligned {dtype}")
+    rng = np.random.default_rng(5)
+    shape = (300, 65, 33)
+
+    def shifted(n):
+        a, t = draw(shape, rng, dtype)
+        s = torch.empty(t.numel() + n, dtype=t.dtype, device=t.device)[n:].view(shape)
+        return a, s.copy_(t)
+
+    (y, yt), (z, zt) = shifted(1), shifted(3)
+    out = torch.empty(yt.numel() + 1, dtype=yt.dtype, device=yt.device)[1:].view(shape)
+    assert yt.data_ptr() % 16 and zt.data_ptr() % 16 and out.data_ptr() % 16
+    vmb.vmb_ss2d_out_norm(yt, zt, None, None, 1e-5, out)
+    torch.cuda.synchronize()
+    ref = oracle.out_norm_gate(y, z, None, None, 1e-5)
+    assert_close(to_f64(out), ref, **(FP32_TOL if dtype == "f32" else BF16_TOL), what="norm")

@@ -1,5 +1,5 @@
-"""Full scan with one wave per sequence (every N but 16, and N = 16 rows of odd
-bf16 length): run, segment and chunk boundaries, channel-slot tails, the fused
+"""Full scan with one wave per sequence (every N but 16, N = 16 in bf16 from 1200
+rows on and of odd length): run, segment and chunk boundaries, channel-slot tails, the fused
 2-D form (planes in LDS, reversed directions whose length is no multiple of a
 run), planes beyond LDS, both types and the zero-order-hold option, against the
 fp64 oracle at the tolerances of the other scans."""
@@ -54,7 +54,8 @@ def test_channel_slot_tails(layout, channels, L):
                      what=f"2d L={L} c={channels}")
 
 
-# the last two maps do not fit LDS in fp32 (24 bytes a pixel) and bf16 (20)
+# 80x85 does not fit LDS in fp32 (16 bytes a pixel), 90x93 in neither type (12 in
+# bf16) with eight states; with one, both do
 MAPS = [(1, 5), (5, 1), (3, 3), (7, 9), (11, 11), (13, 17), (16, 16), (23, 29), (32, 32), (41, 51),
         (80, 85), (90, 93)]
 
@@ -87,7 +88,8 @@ def test_odd_bf16_rows_n16(layout, H, W):
 
 
 # enough rows for two channels a lane (4096 whole-wave sequences, 8192 and
-# 16384 of the segments), with a channel left over, and N = 16 in bf16
+# 16384 of the segments), with a channel left over, and N = 16 in bf16 (its two
+# 2-D cases with one channel a lane)
 @pytest.mark.parametrize("layout,b,H,W,c,N,dtype", [
     ("seq", 9, 1, 515, 115, 4, "f32"), ("2d", 9, 17, 31, 115, 1, "bf16"),
     ("2d", 9, 13, 15, 229, 2, "f32"), ("seq", 9, 9, 9, 457, 1, "bf16"),
@@ -122,6 +124,38 @@ def test_row_limits_n16(layout, b, c, H, W):
         ref, scale = merged_oracle(inp, "full")
         assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
                      what=f"2d {H}x{W} c={c}")
+
+
+# planes beyond LDS, two channels a lane (one left over): columns gathered from
+# the plane (N = 1, 8) or read from its column-major copy (N = 16), sampled channels
+@pytest.mark.parametrize("H,W,N,dtype", [(72, 97, 8, "bf16"), (80, 86, 16, "bf16"),
+                                         (104, 104, 1, "f32"), (72, 73, 4, "f32")])
+def test_large_planes_two_channels(H, W, N, dtype):
+    c = 1025
+    log(f"rows large planes {H}x{W} c={c} N={N} {dtype}")
+    inp = inputs(1, H, W, c, N, "2d", dtype, d_value=1.0)
+    got = to_f64(run_scan(inp, "full", "2d", out_dtype=torch.float32))
+    ds = [0, 1, 2, 7, 8, 511, 1022, 1023, 1024]
+    u = oracle.cross_scan(inp.x)
+    seq = oracle.full_scan(u, inp.delta, inp.A, inp.B, inp.C, inp.D, inp.dt_bias, True,
+                           sel=[k * c + d for k in range(4) for d in ds])
+    seq = np.ascontiguousarray(seq.reshape(1, 4, len(ds), H * W))
+    ref, scale = (oracle.cross_merge(a, H, W, "f64") for a in (seq, np.abs(seq)))
+    assert_close(got[:, ds], ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
+                 what=f"large planes {H}x{W} N={N}")
+
+
+# the same with one channel a lane, and the vector merge to bf16 (whole vectors)
+@pytest.mark.parametrize("H,W,N,dtype", [(104, 108, 1, "f32"), (116, 120, 1, "bf16"),
+                                         (100, 132, 8, "bf16"), (100, 132, 16, "bf16")])
+def test_large_planes(H, W, N, dtype):
+    log(f"rows large planes {H}x{W} N={N} {dtype}")
+    inp = inputs(1, H, W, 3, N, "2d", dtype, d_value=1.0)
+    got = to_f64(run_scan(inp, "full", "2d"))
+    ref, scale = merged_oracle(inp, "full")
+    tol = BF16_TOL if dtype == "bf16" else FP32_TOL
+    assert_close(got, ref, rtol=tol["rtol"], atol=4 * tol["atol"], scale=scale,
+                 what=f"large planes {H}x{W} N={N}")
 
 
 @pytest.mark.parametrize("N", [1, 8])
@@ -210,7 +244,8 @@ def test_growing_small_state():
 
 # A = -inf forgets the state at every position; a plane whose length is no
 # multiple of a run has identity positions ahead of its reversed directions
-@pytest.mark.parametrize("layout,H,W", [("2d", 7, 9), ("2d", 11, 11), ("2d", 23, 29), ("seq", 1, 513)])
+@pytest.mark.parametrize("layout,H,W", [("2d", 7, 9), ("2d", 11, 11), ("2d", 23, 29),
+                                        ("seq", 1, 513)])
 def test_infinite_decay(layout, H, W):
     log(f"rows A = -inf {layout} {H}x{W}")
     inp = inputs(1, H, W, 5, 2, layout)

@@ -19,6 +19,7 @@ from test_gpu_scan import merged_oracle
 pytestmark = pytest.mark.gpu
 
 MIN_ROWS = 16384  # batch * 4 * channels from which the tile path runs
+MIN_ROWS_BF16 = 49152  # the same for bf16 rows of more than 64 elements
 
 
 def inputs(batch, H, W, channels, layout="seq", dtype="f32", seed=0, d_value=1.0):
@@ -76,6 +77,23 @@ def test_2d_layout(H, W, dtype):
     assert_close(got, ref, rtol=FP32_TOL["rtol"], atol=4 * FP32_TOL["atol"], scale=scale,
                  what=f"2d {H}x{W} {dtype}")
     del tol
+
+
+# bf16 rows that the tile kernel takes (even lengths), with a last tile that is
+# not whole: with the column-major copy (L >= 128) and without, and up to 64
+# elements
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+@pytest.mark.parametrize("batch,H,W", [(12, 14, 14), (12, 6, 13), (4, 6, 9), (4, 5, 4)])
+def test_2d_layout_bf16(batch, H, W, out):
+    assert batch * 4 * 1024 >= (MIN_ROWS_BF16 if H * W > 64 else MIN_ROWS)
+    log(f"tiles full 2d bf16 {H}x{W} -> {out}")
+    inp = inputs(batch, H, W, 1024, layout="2d", dtype="bf16", seed=H * 100 + W)
+    got = to_f64(run_scan(inp, "full", "2d",
+                          out_dtype=torch.bfloat16 if out == "bf16" else torch.float32))
+    ref, scale = merged_oracle(inp, "full")
+    tol = BF16_TOL if out == "bf16" else FP32_TOL
+    assert_close(got, ref, rtol=tol["rtol"], atol=4 * tol["atol"], scale=scale,
+                 what=f"2d bf16 {H}x{W} -> {out}")
 
 
 @pytest.mark.parametrize("use_bias,use_d,softplus", [(False, True, True), (True, False, True),

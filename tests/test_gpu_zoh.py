@@ -1,7 +1,7 @@
 """The zero-order-hold B-bar option (VMB_SCAN_ZOH: eq. 4's second line as
 (Delta A)^-1 (exp(Delta A) - I) Delta B) of the full scan against the fp64
 oracle's ZOH scan: the tile kernel (N = 16, any number of rows, tile
-boundaries, bf16), the lane kernel (other N, and N = 16 below one tile), the
+boundaries, bf16), one wave per sequence (other N, and N = 16 below one tile), the
 2-D layout; D = 0 cases show the B term alone. A and D differ per channel, and
 the timescale reaches both sides of the series/direct switch at |Delta A| =
 0.02 (softplus(dt_bias) spans 1e-3 .. 1e-1, A = -(n + 1) scaled per channel)."""
@@ -37,7 +37,7 @@ CASES = [
     ("tiles_b4_c1024_L40", dict(b=4, H=5, W=8, c=1024, N=16)),
     ("tiles_b2_c70_L33", dict(b=2, H=3, W=11, c=70, N=16)),
     ("tiles_b1_c8_L3136", dict(b=1, H=56, W=56, c=8, N=16)),
-    # lane kernel: other N, and N = 16 below one tile
+    # one wave per sequence: other N, and N = 16 below one tile
     ("lanes_n4_L49", dict(b=2, H=7, W=7, c=40, N=4)),
     ("lanes_n1_L60", dict(b=1, H=6, W=10, c=9, N=1)),
     ("lanes_n8_L200", dict(b=1, H=10, W=20, c=65, N=8)),
@@ -64,7 +64,7 @@ def test_zoh_differs_from_first_order():
 
 
 @pytest.mark.parametrize("out", ["bf16", "f32"])
-@pytest.mark.parametrize("L", [48, 49])  # 49: odd, bf16 takes the lane kernel
+@pytest.mark.parametrize("L", [48, 49])  # 49: odd, bf16 takes one wave per sequence
 def test_bf16(L, out):
     log(f"zoh full bf16 L={L} -> {out}")
     inp = inputs(2, 1, L, 40, 16, dtype="bf16", seed=600 + L)
