@@ -18,8 +18,8 @@
 // is the operand of column block j, so column c of block j is position
 // VP c + j of the wave's 16 VP positions. That permutation of the positions
 // makes every load and store of a row one contiguous segment of 16 VP
-// elements, needs no transpose and, since a column never mixes with another,
-// no LDS and no barrier. The order in which the contraction runs over the
+// elements and, since a column never mixes with another, needs no transpose
+// through LDS. The order in which the contraction runs over the
 // channels is free as well: a lane group takes the channels whose weights are
 // consecutive in memory (one vector load of W).
 //   1. x_dbl: steps of 16 (fp32) or 32 (bf16) channels, the next step's u and
@@ -29,8 +29,8 @@
 //      the rounded remainder), and the two products per row block are exact in
 //      fp32, so W is carried to about 2^-17 of itself (far below the bf16
 //      rounding of the outputs).
-//      With KS > 1 the KS waves of a tile take every KS-th step and their sums
-//      meet in LDS, added in wave order.
+//      The KS waves of a tile take every KS-th step and their sums meet in
+//      LDS, added in a fixed order.
 //   2. delta: the accumulator of x_dbl row 4 q + v of a block, held by lane
 //      group q, is used as it is as the operand of contraction step v (whose
 //      four indices are then the rows v, 4 + v, 8 + v, 12 + v), against the
@@ -107,12 +107,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
     const T* __restrict__ u, const float* __restrict__ W, const float* __restrict__ Wdt,
     T* __restrict__ delta, T* __restrict__ Bo, T* __restrict__ Co, int K, int Dc, int L, int N,
     int R, int64_t groups, int tiles) {
+    static_assert(KS == 2 || KS == 4, "two or four waves share a tile");
     constexpr int PW = kWaves / KS;  // tiles per workgroup
     constexpr int kStep = step_channels<T>();
     constexpr int kCh = kStep / 4;
     constexpr int NB = 2;            // step buffers: one step in flight
     constexpr int kRegs = MB * VP;   // accumulators (4 registers each) of a tile
-    __shared__ float part[KS > 1 ? kWaves / 2 * kRegs * 256 : 1];
+    __shared__ float part[kWaves / 2 * kRegs * 256];
 
     const int nwg = static_cast<int>(gridDim.x), wg = static_cast<int>(blockIdx.x);
     const int q = nwg / 8, rem = nwg % 8, xcd = wg % 8;
@@ -122,8 +123,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
     const int pw = wv % PW, ks = wv / PW;
     const int wgs_k = (tiles + PW - 1) / PW;  // workgroups per direction
     const int k = logical / wgs_k;
+    // (the waves of a tile past the last work on its last position and return
+    // after the join)
     const int tile = (logical - k * wgs_k) * PW + pw;
-    if (KS == 1 && tile >= tiles) return;  // KS > 1: PW tiles divide evenly or PW == 1
     const int col = lane & 15, kq = lane >> 4;
     const int M = R + 2 * N;  // (M + 15) / 16 == MB
     const size_t l = static_cast<size_t>(L);
@@ -287,49 +289,47 @@ __global__ __launch_bounds__(kThreads, 2) void k_projections(
         multiply(s);
     }
     const int rblocks = (R + 15) / 16;
-    if constexpr (KS > 1) {
-        // The sums of the tile's waves: the upper half hands its own to the
-        // lower, then each wave adds the KS / 2 pair sums for the blocks it
-        // goes on with (the timescale rows, and its share of the B and C
-        // rows). Half the LDS of one slot a wave.
-        constexpr int kHalf = KS / 2;
-        auto slot = [&](int w, int mb, int j) {
-            return reinterpret_cast<f32x4*>(part + (pw * kHalf + w) * kRegs * 256 +
-                                            ((mb * VP + j) * 64 + lane) * 4);
-        };
-        if (ks >= kHalf) {
+    // The sums of the tile's waves: the upper half hands its own to the
+    // lower, then each wave adds the KS / 2 pair sums for the blocks it
+    // goes on with (the timescale rows, and its share of the B and C
+    // rows). Half the LDS of one slot a wave.
+    constexpr int kHalf = KS / 2;
+    auto slot = [&](int w, int mb, int j) {
+        return reinterpret_cast<f32x4*>(part + (pw * kHalf + w) * kRegs * 256 +
+                                        ((mb * VP + j) * 64 + lane) * 4);
+    };
+    if (ks >= kHalf) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int j = 0; j < VP; ++j) *slot(ks - kHalf, mb, j) = acc[mb][j];
-        }
-        __syncthreads();
-        if (ks < kHalf) {
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int j = 0; j < VP; ++j) *slot(ks, mb, j) += acc[mb][j];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            if (mb >= rblocks && mb % KS != ks) continue;
-#pragma unroll
-            for (int j = 0; j < VP; ++j) {
-                f32x4 s = *slot(0, mb, j);
-#pragma unroll
-                for (int w = 1; w < kHalf; ++w) s += *slot(w, mb, j);
-                acc[mb][j] = s;
-            }
-        }
-        if (tile >= tiles) return;
+            for (int j = 0; j < VP; ++j) *slot(ks - kHalf, mb, j) = acc[mb][j];
     }
+    __syncthreads();
+    if (ks < kHalf) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int j = 0; j < VP; ++j) *slot(ks, mb, j) += acc[mb][j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        if (mb >= rblocks && mb % KS != ks) continue;
+#pragma unroll
+        for (int j = 0; j < VP; ++j) {
+            f32x4 s = *slot(0, mb, j);
+#pragma unroll
+            for (int w = 1; w < kHalf; ++w) s += *slot(w, mb, j);
+            acc[mb][j] = s;
+        }
+    }
+    if (tile >= tiles) return;
 
     // B and C rows
     if (ok) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            if (KS > 1 && mb % KS != ks) continue;
+            if (mb % KS != ks) continue;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * mb + 4 * kq + v;

@@ -1,5 +1,6 @@
 // scan_rows.hip -- full selective scan, one wave per sequence (any N; the
-// path of every N but 16, and of the N = 16 forms the other kernels refuse).
+// path of every N but 16, of N = 16 in bf16 between 1200 and 49152 rows, and of
+// the N = 16 forms the other kernels refuse: bf16 rows of odd length).
 //
 // Same recurrence as scan_full.hip (Appendix A: eq. 3, eq. 4 first line,
 // eq. 6). Lanes own runs of T = 8 (or 4) consecutive positions; a wave walks
@@ -32,6 +33,8 @@
 // aligned vectors: the reversed directions start their runs at the padded end
 // of the plane, with identity positions (Delta = 0, B = 0) ahead of the first
 // pixel.
+//
+// Values that are not finite: see walk_positions.
 #include "vmb_internal.h"
 
 namespace vmb {

@@ -107,9 +107,9 @@ struct MeanWsLayout {
     size_t scan, rmean, agg, carry, ytil, xt, flags, gpart, total;
 };
 // Short planes (a few cache lines) are gathered directly instead: the copy
-// pass costs more than it saves there. Planes beyond LDS are copied in 32 x 32
-// tiles (2 x 128 x 512: the copy takes 55 us, the column gathers it replaces
-// about 200 us of the reduce).
+// pass costs more than it saves there. Planes beyond LDS are copied in 64 x 64
+// tiles of vectors, or 32 x 32 ones of elements (2 x 128 x 512: the copy takes
+// 33 us, the column gathers it replaces about 200 us of the reduce).
 constexpr int64_t kMeanTransposeMinL = 256;
 inline bool mean_transposes(int64_t L, bool two_d) {
     return two_d && L >= kMeanTransposeMinL;
@@ -215,7 +215,7 @@ bool use_short_full(const ScanArgs& a);
 vmb_status launch_full_short(const ScanArgs& a, void* y_seq);
 // One wave per sequence, any N (scan_rows.hip); writes a.y in either layout.
 vmb_status launch_full_rows(const ScanArgs& a);
-// Whether the positions-over-lanes kernel is the better fit for this shape.
+// Whether the positions-over-lanes kernel takes this shape.
 bool use_chunked_full(const ScanArgs& a);
 // Channels over lanes, states over the four waves of a workgroup, positions
 // in tiles (N == 16, at least kTilesMinRows batch * K * channels rows);
@@ -227,11 +227,13 @@ bool tiles_take(const ScanArgs& a);
 // planes (xt, written by launch_transpose_planes into the workspace after the
 // per-direction outputs), so directions 1 and 3 load contiguous rows.
 vmb_status launch_full_tiles(const ScanArgs& a, void* y_seq, const void* xt);
-// Full scan, 2-D layout: whether the workspace holds xt (the tile path's
-// shapes with planes of 128 to 6144 positions: below, a plane spans a few
-// cache lines and the column-major reads gather it from L1 faster than a copy
-// pass; and the positions-over-lanes path's sequences of more than one
-// chunk, whose one-chunk form stages the plane in LDS instead), where it
+// Full scan, 2-D layout: whether the workspace holds xt (from kTilesMinRows
+// rows on, the tile path's shapes, planes of 128 to 6144 positions: below, a
+// plane spans a few cache lines and the column-major reads gather it from L1
+// faster than a copy pass; and with fewer rows the positions-over-lanes path's
+// sequences of more than one chunk, whose one-chunk form stages the plane in
+// LDS instead). The one-wave-per-sequence path uses the copies for planes
+// beyond LDS where there is room for them. Where xt
 // starts (after the per-direction fp32 outputs), and its size (4 bytes per
 // element, either input type).
 inline bool full_ws_has_xt(int64_t batch, int64_t K, int64_t channels, int64_t L, int64_t N) {
