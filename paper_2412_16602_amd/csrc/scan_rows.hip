@@ -184,8 +184,7 @@ struct Place {
 // Workgroup i runs on XCD i % 8 (own L2): each XCD takes a contiguous
 // range, so the channels that share B and C rows share an L2.
 template <int kMode, int kPlanes>
-__device__ __forceinline__ Place place_of(const RowArgs& g) {
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+__device__ __forceinline__ Place place_of(const RowArgs& g, int wv) {
     int grp;
     Place p;
     if (g.n_wg) {
@@ -214,24 +213,78 @@ __host__ __device__ inline int row_len(int64_t L, int T) {
     return static_cast<int>((L + T - 1) / T * T);
 }
 
-// The wave's sequences once more, position after position: lane 16 j + n has
-// state n of the j-th of four channels at a time. For waves whose joined runs
-// came out infinite or NaN: a product of factors above 1 over several runs may
-// leave the range of fp32 (0.2 a position over 512 is enough) where the states
-// themselves, zero or small, do not; the identity positions ahead of a reversed
-// plane form 0 A, NaN for an infinite A; and values that are not finite by
-// themselves are to be what the recurrence makes of them. About as slow as a
-// lane per channel, and never reached by states that decay. The kernel's
-// arguments are read again and nothing else of the wave's is used, so that the
-// scan holds no registers for it.
-template <int T, int kPlanes, typename Tin, typename Tout, int kMode, bool kZoh>
-__device__ __forceinline__ void walk_positions(char* lds) {
+// Fused form: the sums of the two scan orders, stored to y, four pixels a
+// thread at a time. Returns 0, or NaN where a sum was not finite.
+template <int T, int kPlanes, typename Tin, typename Tout>
+__device__ __forceinline__ float fold_planes(const RowArgs& g, const Place& place, char* lds) {
+    constexpr int kThr = kRowThreads / kPlanes;  // threads per plane
+    const int ch = threadIdx.x / kThr;
+    if (ch >= place.nc) return 0.0f;
+    const int H = g.H, W = g.W, L = static_cast<int>(g.L), Lp = row_len(L, T);
+    Tout* out =
+        static_cast<Tout*>(g.y) + (static_cast<size_t>(place.b) * g.Dc + place.d0 + ch) * L;
+    const float* y_planes = reinterpret_cast<const float*>(lds + 2 * kPlanes * Lp * sizeof(Tin));
+    const float* yr = y_planes + ch * Lp;
+    const float* yc = y_planes + (kPlanes + ch) * Lp;
+    int p = (threadIdx.x % kThr) * 4;
+    int h = p / W, w = p - h * W;
+    const int dh = 4 * kThr / W, dw = 4 * kThr - dh * W;
+    float bad = 0.0f;
+    for (; p < L; p += 4 * kThr) {
+        const float4 r = *reinterpret_cast<const float4*>(yr + p);  // whole runs: Lp % 4 == 0
+        const float rv[4] = {r.x, r.y, r.z, r.w};
+        float sum[4];
+        Tout o[4];
+        int hh = h, ww = w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sum[i] = rv[i] + yc[p + i < L ? ww * H + hh : 0];
+            o[i] = from_f32<Tout>(sum[i]);
+            if (++ww == W) { ww = 0; ++hh; }
+        }
+        if (p + 4 <= L) {
+            __builtin_memcpy(out + p, o, sizeof(o));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bad = __builtin_fmaf(sum[i], 0.0f, bad);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (p + i < L) {
+                    out[p + i] = o[i];
+                    bad = __builtin_fmaf(sum[i], 0.0f, bad);
+                }
+        }
+        w += dw;
+        h += dh;
+        if (w >= W) { w -= W; ++h; }
+    }
+    return bad;
+}
+
+// The kernel's arguments, read once more: for a path that is hardly ever taken
+// and shall hold no registers in the one that always is.
+__device__ __forceinline__ RowArgs args_again() {
     typedef const __attribute__((address_space(4))) RowArgs* Args;
     Args args = (Args)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
-    const RowArgs g = *(const RowArgs*)args;
-    const Place p = place_of<kMode, kPlanes>(g);
-    const int lane = threadIdx.x % kWave, n = lane % 16, N = g.N;
+    return *(const RowArgs*)args;
+}
+
+// The wave's sequences once more, position after position: lane 16 j + n has
+// state n of the j-th of four channels at a time. For outputs that came out
+// infinite or NaN: a product of factors above 1 over several runs may leave the
+// range of fp32 (0.2 a position over 512 is enough) where the states
+// themselves, zero or small, do not; the identity positions ahead of a reversed
+// plane form 0 A, NaN for an infinite A; and values that are not finite by
+// themselves are to be what the recurrence makes of them. (A state that is not
+// finite makes every output that it enters so, whatever C is.) About as slow as
+// a lane per channel, and never reached by states that decay.
+template <int T, int kPlanes, typename Tin, typename Tout, int kMode, bool kZoh>
+__device__ __forceinline__ void walk_positions(int wv, char* lds) {
+    const RowArgs g = args_again();
+    const Place p = place_of<kMode, kPlanes>(g, wv);
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int n = lane % 16, N = g.N;
     const int64_t L = g.L, bk = static_cast<int64_t>(p.b) * g.K + p.k;
     const Tin* Bn = static_cast<const Tin*>(g.B) + (bk * N + (n < N ? n : 0)) * L;
     const Tin* Cn = static_cast<const Tin*>(g.C) + (bk * N + (n < N ? n : 0)) * L;
@@ -291,7 +344,7 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
     const int Dc = g.Dc, N = kN1 ? 1 : g.N;  // a multiple of NP
     const int64_t L = g.L;
 
-    const Place here = place_of<kMode, kPlanes>(g);
+    const Place here = place_of<kMode, kPlanes>(g, wv);
     const int b = here.b, k = here.k, d0 = here.d0;
     if (kMode != kFused && d0 >= Dc) return;
     const int nc = here.nc;
@@ -418,8 +471,6 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
                        (static_cast<size_t>(b) * Dc + d0 + (ch < nc ? ch : 0)) * iL;
         Tin* pr = u_rows + ch * Lp;
         Tin* pc = u_cols + ch * Lp;
-        if (tid % kThr < Lp - iL)  // finite values past the last pixel
-            pr[iL + tid % kThr] = pc[iL + tid % kThr] = from_f32<Tin>(0.0f);
         for (int p = (tid % kThr) * kPer; p < iL; p += kThr * kPer) {
             Tin v[kPer];
             const int n = iL - p < kPer ? iL - p : kPer;
@@ -452,7 +503,7 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
     float carry[CH];  // lane n: state n leaving the previous chunk
 #pragma unroll
     for (int h = 0; h < CH; ++h) carry[h] = 0.0f;
-    int bad = 0;  // values that are not finite came up
+    int bad = 0;  // outputs that are not finite came up (kFused: see fold_planes)
     for (int64_t c0 = 0; c0 < L + lead; c0 += kChunk) {
         // 1. per-position products of the runs
         int at = 0;  // fused: the run's first element in its plane
@@ -578,13 +629,12 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
                 }
             }
         }
-        // A state that is not finite makes every output that it enters so,
-        // whatever C is, or else (the last run's) the carry.
+        if constexpr (kMode != kFused) {
+            bool any = false;
 #pragma unroll
-        for (int h = 0; h < CH; ++h)
-            if (__builtin_amdgcn_ballot_w64(
-                    !(__builtin_isfinite(yv[h][0]) && __builtin_isfinite(carry[h]))) != 0)
-                bad = 1;
+            for (int h = 0; h < CH; ++h) any |= !__builtin_isfinite(yv[h][0]);
+            if (__builtin_amdgcn_ballot_w64(any) != 0) bad = 1;
+        }
         // 4. outputs
         if constexpr (kMode == kFused) {
             // A plane takes the forward and the reversed direction of its
@@ -631,51 +681,25 @@ __global__ __launch_bounds__(kRowThreads, (row_waves<Tin, CH * NP, kMode>())) vo
     if constexpr (kMode != kFused) {
         if (bad) {
             __threadfence();  // after the stores of the loop above
-            walk_positions<T, kPlanes, Tin, Tout, kMode, kZoh>(nullptr);
+            walk_positions<T, kPlanes, Tin, Tout, kMode, kZoh>(wv, nullptr);
         }
     } else {
         __syncthreads();
+        const float nan = fold_planes<T, kPlanes, Tin, Tout>(g, here, lds);
         // the input planes are no longer read: a word for each wave
         uint32_t* redo = reinterpret_cast<uint32_t*>(lds);
-        if (lane == 0) redo[wv] = bad;
+        const bool any = __builtin_amdgcn_ballot_w64(nan != 0.0f) != 0;
+        if (lane == 0) redo[wv] = any;
         __syncthreads();
         if (redo[0] | redo[1] | redo[2] | redo[3]) {
+            __threadfence();  // after the stores above
 #pragma unroll 1
             for (int pass = 0; pass < 2; ++pass) {  // forward directions first
-                if (rev == (pass == 1)) walk_positions<T, kPlanes, Tin, Tout, kMode, kZoh>(lds);
+                if (rev == (pass == 1)) walk_positions<T, kPlanes, Tin, Tout, kMode, kZoh>(wv, lds);
                 __syncthreads();
             }
-        }
-        const int H = g.H, W = g.W;
-        constexpr int kThr = kRowThreads / kPlanes;  // threads per plane, 4 pixels each
-        const int ch = tid / kThr;
-        if (ch >= nc) return;
-        Tout* out = static_cast<Tout*>(g.y) + (static_cast<size_t>(b) * Dc + d0 + ch) * iL;
-        const float* yr = y_planes + ch * Lp;
-        const float* yc = y_planes + (kPlanes + ch) * Lp;
-        int p = (tid % kThr) * 4;
-        int h = p / W, w = p - h * W;
-        const int dh = 4 * kThr / W, dw = 4 * kThr - dh * W;
-        for (; p < iL; p += 4 * kThr) {
-            const float4 r = *reinterpret_cast<const float4*>(yr + p);  // whole runs: Lp % 4 == 0
-            const float rv[4] = {r.x, r.y, r.z, r.w};
-            Tout o[4];
-            int hh = h, ww = w;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                o[i] = from_f32<Tout>(rv[i] + yc[p + i < iL ? ww * H + hh : 0]);
-                if (++ww == W) { ww = 0; ++hh; }
-            }
-            if (p + 4 <= iL) {
-                __builtin_memcpy(out + p, o, sizeof(o));
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (p + i < iL) out[p + i] = o[i];
-            }
-            w += dw;
-            h += dh;
-            if (w >= W) { w -= W; ++h; }
+            const RowArgs again = args_again();
+            fold_planes<T, kPlanes, Tin, Tout>(again, place_of<kMode, kPlanes>(again, wv), lds);
         }
     }
 }
