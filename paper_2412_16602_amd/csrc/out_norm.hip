@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void k_out_norm(const T* __restrict__ y,
 // y and z loads in flight at once. Bound by HBM: 128 x 56x56, 192 channels,
 // bf16: 187 us with one pixel a lane (32- to 64-byte segments), 126 with
 // vectors (3.7 TB/s); 32 x 56x56, fp32 77 -> 54 (4.3 TB/s); 32 x 28x28, 384
-// channels 37 -> 32. An image's pixels are taken in groups of V; its last group starts at
+// channels 36 -> 30.5. An image's pixels are taken in groups of V; its last group starts at
 // P - V and forms the pixels it shares with the one before a second time, to
 // the same bits.
 constexpr int kVecGroups = 64;

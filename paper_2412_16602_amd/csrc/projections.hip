@@ -39,11 +39,11 @@
 // What bounds it (32 x 28x28, 384 channels, rank 12, fp32, 308 MB of u and
 // delta): the same tile-wise copy without products takes 72 us (4.3 TB/s; 58 us
 // in linear order) and the products 33 us at the fp32 matrix rate; they
-// overlap only in part, 100 us (127 with u and W staged in LDS behind two
+// overlap only in part, 93 us (128 with u and W staged in LDS behind two
 // barriers per 64 channels, and the low-rank product through LDS). More steps
 // in flight (2 or 3) or three or four waves a SIMD measured no faster.
-// 32 x 14x14, 768 channels, rank 24, bf16: 103 -> 39 us; 128 x 56x56, 192
-// channels, rank 6, bf16: 527 -> 313 us.
+// 32 x 14x14, 768 channels, rank 24, bf16: 103 -> 36 us; 128 x 56x56, 192
+// channels, rank 6, bf16: 523 -> 309 us.
 // Positions are taken in groups of VP per sequence; the last group of a
 // sequence starts at L - VP and forms the positions it shares with the group
 // before a second time, to the same bits. 16x16 accumulators: register v of
@@ -477,8 +477,9 @@ void launch_vp(const Args& a) {
     }
 }
 
-// Tile width and channel split. Measured (us; four waves a tile, two, one, or
-// two positions a lane and four waves), VMamba stages at batch 32:
+// Tile width and channel split. Measured when they were chosen (us; four waves a
+// tile, two, one, or two positions a lane and four waves; since then the
+// addressing took 3 to 7% off the fp32 rows), VMamba stages at batch 32:
 //   28x28 fp32 rank 12      1568 tiles   100  112  107  111
 //   14x14 bf16 rank 24       392 tiles    39   42   68   48
 //   7x7 fp32 rank 48         104 tiles    66  122  232   45
