@@ -120,7 +120,10 @@ vmb_status vmb_cross_merge(const void* ys, void* y, int64_t batch, int64_t chann
  *
  *   u        : in_dtype, [batch, K, channels, L] (SEQ) or x [batch, channels, H, W] (2D)
  *   delta    : in_dtype, [batch, K, channels, L]
- *   A        : float32,  [K*channels, N]  (negative for a decaying state)
+ *   A        : float32,  [K*channels, N]  (negative for a decaying state; with
+ *              N = 16 some kernels join runs of up to 3328 positions by the
+ *              product of their factors exp(Delta A): where factors above 1
+ *              take that product beyond float32, a zero state becomes NaN)
  *   B, C     : in_dtype, [batch, K, N, L]
  *   D        : float32,  [K*channels] or NULL (treated as 0)
  *   dt_bias  : float32,  [K*channels] or NULL (treated as 0)
